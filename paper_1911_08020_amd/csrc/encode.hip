@@ -189,25 +189,41 @@ __device__ __forceinline__ void small_blocks_all(const Vec<Bits, VEC> (&v)[UNROL
                                     nblk, values, offsets);
 }
 
-template <typename Bits, bool ALIGNED>
+// 16 bytes of a row at any element address: global loads need no alignment on gfx950,
+// so a row whose start is not a multiple of 16 bytes (N odd, an offset view) still takes
+// one load instruction per vector.
+template <typename Bits> struct RowVec;
+template <> struct RowVec<uint32_t> {
+    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <> struct RowVec<uint16_t> {
+    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(2)));
+};
+
+// Waves take (row, chunk) pairs one after the other, so a workgroup's four waves cover
+// several rows when a row is shorter than four chunks: a workgroup per row and four
+// chunks left three of four waves idle on rows of one chunk.  Bound: the HBM stream of W.
+// 6000 x 1500 fp16 (rows 3000 bytes apart, 18 MB): 12.5 us with element loads and a
+// workgroup per row, 7.3 us so; 4096 x 9216 fp32 (151 MB): 26.1 us either way, 6.1 TB/s.
+template <typename Bits>
 __global__ __launch_bounds__(kEncodeThreads) void encode_kernel(
     const Bits *__restrict__ W, int64_t ldw, int64_t N, const int64_t *__restrict__ rowinfo,
-    int64_t chunks_per_row, int cgroups, Bits *__restrict__ values,
+    uint32_t chunks_per_row, uint32_t total_chunks, Bits *__restrict__ values,
     uint8_t *__restrict__ offsets) {
     using Tr = EncodeTraits<Bits>;
     constexpr int VEC = Tr::VEC;
     constexpr int UNROLL = Tr::UNROLL;
     constexpr int64_t CHUNK = int64_t(kWave) * VEC * UNROLL;
 
-    // workgroup -> (original row r, group of kEncodeWaves chunks); all uniform.  The
-    // W loads depend on nothing but r, so they issue first; the row's block size and
-    // first output slot arrive from the per-row table while they are in flight.
-    const int r = int(blockIdx.x) / cgroups;
-    const int cg = int(blockIdx.x) - r * cgroups;
+    // wave -> (original row r, chunk q of it); all uniform.  The W loads depend on
+    // nothing but r, so they issue first; the row's block size and first output slot
+    // arrive from the per-row table while they are in flight.
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
     const int lane = int(threadIdx.x) & (kWave - 1);
-    const int64_t q = int64_t(cg) * kEncodeWaves + wave;
-    if (q >= chunks_per_row) return;                  // wave-uniform, no barrier below
+    const uint32_t item = blockIdx.x * uint32_t(kEncodeWaves) + uint32_t(wave);
+    if (item >= total_chunks) return;                 // wave-uniform, no barrier below
+    const uint32_t r = item / chunks_per_row;
+    const int64_t q = int64_t(item - r * chunks_per_row);
     const Bits *row = W + int64_t(r) * ldw;
     const int64_t info = rowinfo[r];
 
@@ -216,9 +232,9 @@ __global__ __launch_bounds__(kEncodeThreads) void encode_kernel(
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
         const int64_t c0 = q * CHUNK + int64_t(u) * (kWave * VEC) + int64_t(lane) * VEC;
-        if (ALIGNED && c0 + VEC <= N) {
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + c0));
+        if (c0 + VEC <= N) {
+            typedef typename RowVec<Bits>::T RV;
+            const RV t = __builtin_nontemporal_load(reinterpret_cast<const RV *>(row + c0));
             v[u] = __builtin_bit_cast(Vec<Bits, VEC>, t);
         } else {
 #pragma unroll
@@ -255,21 +271,12 @@ hipError_t launch_encode_t(const darb_plan &p, const void *W, int64_t ldw, void 
     using Tr = EncodeTraits<Bits>;
     constexpr int64_t CHUNK = int64_t(kWave) * Tr::VEC * Tr::UNROLL;
     const int64_t chunks = (p.N + CHUNK - 1) / CHUNK;
-    const int64_t cgroups = (chunks + kEncodeWaves - 1) / kEncodeWaves;
-    const int64_t blocks = p.M * cgroups;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    const bool aligned = (reinterpret_cast<uintptr_t>(W) % 16 == 0) &&
-                         ((ldw * int64_t(sizeof(Bits))) % 16 == 0);
-    const Bits *w = static_cast<const Bits *>(W);
-    Bits *vals = static_cast<Bits *>(values);
-    if (aligned)
-        hipLaunchKernelGGL((encode_kernel<Bits, true>), dim3(unsigned(blocks)),
-                           dim3(kEncodeThreads), 0, s, w, ldw, p.N, p.d_rowinfo, chunks,
-                           int(cgroups), vals, offsets);
-    else
-        hipLaunchKernelGGL((encode_kernel<Bits, false>), dim3(unsigned(blocks)),
-                           dim3(kEncodeThreads), 0, s, w, ldw, p.N, p.d_rowinfo, chunks,
-                           int(cgroups), vals, offsets);
+    const int64_t total = p.M * chunks;
+    const int64_t blocks = (total + kEncodeWaves - 1) / kEncodeWaves;
+    if (blocks > 0x3FFFFFFF) return hipErrorInvalidConfiguration;   // total fits 32 bits
+    hipLaunchKernelGGL((encode_kernel<Bits>), dim3(unsigned(blocks)), dim3(kEncodeThreads), 0, s,
+                       static_cast<const Bits *>(W), ldw, p.N, p.d_rowinfo, uint32_t(chunks),
+                       uint32_t(total), static_cast<Bits *>(values), offsets);
     return hipGetLastError();
 }
 
