@@ -321,13 +321,19 @@ int darb_prune_counts_noalloc(int64_t M, int64_t N, int wdtype, const void *W, i
  *   c_t = sigmoid(f) * c_{t-1} + sigmoid(i) * tanh(g),  h_t = sigmoid(o) * tanh(c_t).
  * W_ih is [4H x I] and W_hh is [4H x H], both of wdtype, each with its own
  * uploaded plan.  The input products of all steps are computed first as one
- * darb_spmm with B = T * batch.  Each time step is then one launch: a workgroup per
+ * darb_spmm with B = T * batch.  The time steps then run as one launch whose
+ * workgroups keep W_hh and exchange h through the workspace (T >= 16, batch <= 64, W_hh
+ * rows of at most 512 retained weights, H up to about 4000 at batch <= 32, not under
+ * stream capture).  Such launches follow each other on a device whatever their streams;
+ * a workgroup's waits are bounded, and a sequence whose workgroups could not all run at
+ * once (another process holding the device) is computed again without waiting, with the
+ * same result bit for bit.  Otherwise each time step is one launch: a workgroup per
  * hidden unit computes the unit's four gate rows of W_hh h_{t-1} and the cell
  * (batch <= 64 and a multiple of 4, or batch <= 16; W_hh rows of at most 512
  * retained weights); other shapes run
- * the recurrent product and the cell as two launches.  Both give the same result
+ * the recurrent product and the cell as two launches.  All give the same result
  * within the product tolerance; the call is deterministic.  The workspace also
- * holds the second buffer of h that the steps alternate with `h`.
+ * holds the second buffer of h that the steps alternate with `h`, or the exchange's.
  *   x_seq      device fp32 [I x T*batch], column t*batch + n
  *   h_seq      device fp32 [H x T*batch], receives h_t in columns t*batch + n
  *   h, c       device fp32 [H x batch], initial state in, final state out

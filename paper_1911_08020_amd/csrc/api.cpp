@@ -655,7 +655,8 @@ static int lstm_check(const darb_plan *wih, const void *wih_values, const uint8_
     return DARB_OK;
 }
 
-// The time steps.  When every gate row of the recurrent matrix fits the fused
+// The time steps: all in one launch where that applies (lstm_seq.hip; G is its scratch).
+// Otherwise, when every gate row of the recurrent matrix fits the fused
 // step kernel, one launch per step computes the product and the cell of every
 // hidden unit, reading h from one buffer and writing the other (h and, as the
 // second buffer, the first H x batch floats of G); otherwise two launches per
@@ -664,6 +665,9 @@ static int lstm_steps(const darb_plan *whh, const void *whh_values, const uint8_
                       int wdtype, int64_t H, int64_t T, int64_t batch, const float *U, float *G,
                       float *h_seq, float *h, float *c, hipStream_t s) {
     const int64_t TB = T * batch;
+    if (lstm_seq_applies(*whh, H, T, batch, s))
+        return launched(launch_lstm_seq(*whh, wdtype, whh_values, whh_offsets, H, T, batch, U, G,
+                                        h_seq, h, c, kLstmMaxPolls, s), "lstm sequence");
     if (lstm_step_fusable(*whh, batch, h, G)) {
         float *hb[2] = {h, G};
         for (int64_t t = 0; t < T; ++t) {

@@ -106,6 +106,17 @@ hipError_t launch_lstm_step(const darb_plan &whh, int wdtype, const void *values
                             const uint8_t *offsets, int64_t H, int64_t batch, const float *h_in,
                             const float *U, int64_t ldu, float *c, float *h_out, float *h_seq,
                             int64_t ld_seq, hipStream_t s);
+// All time steps of the recurrent part in one launch (and a short one before and after),
+// when lstm_seq_applies: U holds the input products [4H x T*batch], scratch 4*H*batch
+// floats (16-byte aligned); h and c are read, and written at the end.  A workgroup waits
+// for the others' part of a step at most max_polls reads (about half a microsecond each)
+// before the sequence is computed without waiting.
+constexpr uint32_t kLstmMaxPolls = 1u << 16;
+bool lstm_seq_applies(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, hipStream_t s);
+hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
+                           const uint8_t *offsets, int64_t H, int64_t T, int64_t batch,
+                           const float *U, float *scratch, float *h_seq, float *h, float *c,
+                           uint32_t max_polls, hipStream_t s);
 hipError_t launch_lstm_cell(int64_t H, int64_t batch, const float *G, const float *U,
                             int64_t ldu, float *h, float *c, float *h_seq, int64_t ld_seq,
                             hipStream_t s);

@@ -55,3 +55,159 @@ def test_encode_chunk_edges_any_alignment(darb, dtype, N, skip):
     ut = np.uint32 if dtype == np.float32 else np.uint16
     assert np.array_equal(host(o), orf)
     assert np.array_equal(host(v).view(ut), vr.view(ut))
+
+
+# --------------------------------------------------------------------------------
+# the LSTM layer's time steps as one launch: batch groups of 1, 2, 4 and 8 columns (the
+# last one partly filled), one to many units per workgroup, odd H, more weights than a
+# workgroup's registers hold (b = 1 rows), final states after any T
+# --------------------------------------------------------------------------------
+
+def _lstm_mats(darb, H, I, dtype, b_min, b_max, keep, seed):
+    rng = np.random.default_rng(seed)
+    dense, dev_mats = [], []
+    for n in (I, H):
+        W = (0.1 * rng.standard_normal((4 * H, n))).astype(dtype)
+        d = np.clip(keep * rng.lognormal(0.0, 0.5, size=4 * H), 0.0, 1.0)
+        plan = darb.Plan(4 * H, n, d, keep, 0, b_min, b_max).upload()
+        lay = oracle.plan(n, d, keep, 0, b_min, b_max)
+        v, o = plan.encode(dev(W))
+        vr, orf = oracle.encode(W, lay)
+        assert np.array_equal(host(o), orf)
+        dense.append(oracle.decode(vr, orf, lay).astype(np.float64))
+        dev_mats.append((plan, v, o))
+    return dense, dev_mats, rng
+
+
+def _lstm_reference(wih, whh, x, h, c, T, B):
+    u = wih @ x.astype(np.float64)
+    H = h.shape[0]
+    seq = np.empty((H, T * B))
+    sig = lambda z: 1.0 / (1.0 + np.exp(-z))  # noqa: E731
+    for t in range(T):
+        z = whh @ h + u[:, t * B:(t + 1) * B]
+        c = sig(z[H:2 * H]) * c + sig(z[:H]) * np.tanh(z[2 * H:3 * H])
+        h = sig(z[3 * H:]) * np.tanh(c)
+        seq[:, t * B:(t + 1) * B] = h
+    return seq, h, c
+
+
+# a gate sums at most 512 + 512 products of weights of about 0.1 and states below 1
+# (inputs of about 1): sum |w x| < 100, each rounding 2^-24, halved on average by the
+# cell: well below 1e-4 after the decay of earlier steps' errors
+LSTM_TOL = 1e-4
+
+
+@pytest.mark.parametrize("case", [
+    # H, I, T, B, dtype, b_min, b_max, keep
+    (16, 24, 16, 2, "f32", 4, 32, 0.1), (33, 16, 17, 2, "f16", 4, 32, 0.1),
+    (128, 64, 18, 1, "f16", 4, 64, 0.06), (96, 40, 16, 9, "f32", 4, 64, 0.1),
+    (200, 64, 19, 16, "f16", 8, 128, 0.06), (130, 32, 16, 17, "f32", 4, 64, 0.1),
+    (512, 64, 17, 20, "f32", 1, 4, 0.9), (512, 32, 16, 32, "f16", 1, 2, 0.9),
+    (1024, 64, 16, 64, "f16", 4, 64, 0.05), (256, 64, 20, 40, "f32", 4, 64, 0.1),
+    (1500, 64, 16, 20, "f16", 4, 64, 0.06), (64, 32, 15, 8, "f32", 4, 32, 0.1)])
+def test_lstm_sequence_launch(darb, case):
+    H, I, T, B, dt, b_min, b_max, keep = case
+    say(f"lstm sequence {case}")
+    dtype = np.float32 if dt == "f32" else np.float16
+    (wih, whh), (dih, dhh), rng = _lstm_mats(darb, H, I, dtype, b_min, b_max, keep, H + B)
+    x = rng.standard_normal((I, T * B)).astype(np.float32)
+    h0 = (0.5 * rng.standard_normal((H, B))).astype(np.float32)
+    c0 = rng.standard_normal((H, B)).astype(np.float32)
+    seq, h, c = darb.lstm_layer(dih, dhh, dev(x), H, T, B, h=dev(h0), c=dev(c0))
+    rs, rh, rc = _lstm_reference(wih, whh, x, h0.astype(np.float64), c0.astype(np.float64), T, B)
+    for got, want, name in ((seq, rs, "h_seq"), (h, rh, "h"), (c, rc, "c")):
+        err = float(np.abs(host(got) - want).max())
+        say(f"  {name}: max abs err {err:.2e}")
+        assert err <= LSTM_TOL, name
+    assert np.array_equal(host(h), host(seq)[:, (T - 1) * B:])
+    # the same bits again, with the buffers as the first call left them
+    again = darb.lstm_layer(dih, dhh, dev(x), H, T, B, h=dev(h0), c=dev(c0))
+    for a, b in zip((seq, h, c), again):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("case", [(96, 16, 9, "f32", 4, 64, 0.1), (520, 17, 20, "f16", 4, 64, 0.1),
+                                  (512, 18, 18, "f32", 1, 2, 0.9)])
+def test_lstm_sequence_without_waiting(darb, case):
+    # a workgroup allowed no wait gives up at once and the last launch computes the
+    # sequence by itself: the same bits
+    import ctypes
+    H, T, B, dt, b_min, b_max, keep = case
+    say(f"lstm sequence recomputed {case}")
+    dtype = np.float32 if dt == "f32" else np.float16
+    _, (_, (plan, v, o)), rng = _lstm_mats(darb, H, H, dtype, b_min, b_max, keep, 5)
+    U = dev(rng.standard_normal((4 * H, T * B)).astype(np.float32))
+    outs = []
+    for polls in (1 << 16, 0):
+        h = dev((0.5 * np.random.default_rng(1).standard_normal((H, B))).astype(np.float32))
+        c = dev(np.random.default_rng(2).standard_normal((H, B)).astype(np.float32))
+        seq = torch.zeros(H, T * B, device="cuda")
+        scratch = torch.zeros(4 * H * B, device="cuda")
+        # darb::launch_lstm_seq (darb_internal.h), which the public call reaches with a limit
+        f = getattr(darb.lib(), "_ZN4darb15launch_lstm_seqERK9darb_planiPKvPKhlllPKfPfS9_S9_S9_j"
+                                "P12ihipStream_t")
+        P = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+        I64 = ctypes.c_int64
+        rc = f(plan.handle, ctypes.c_int(0 if dt == "f32" else 1), P(v), P(o), I64(H), I64(T),
+               I64(B), P(U), P(scratch), P(seq), P(h), P(c), ctypes.c_uint32(polls),
+               ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        torch.cuda.synchronize()
+        failed = int(scratch.view(torch.int32)[_seq_flag(H, B)])
+        assert failed == (1 if polls == 0 else 0)
+        outs.append((seq, h, c))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+def _seq_flag(H, B):
+    """The failure flag's place in the scratch: after three slots of h."""
+    cpg = 1 if B <= 8 else 2 if B <= 16 else 4 if B <= 32 else 8
+    return 3 * H * (-(-B // cpg) * cpg)
+
+
+def test_lstm_sequences_on_several_streams(darb):
+    say("lstm sequences on three streams")
+    H, T, B = 256, 40, 16
+    _, (dih, dhh), rng = _lstm_mats(darb, H, 64, np.float16, 4, 64, 0.06, 3)
+    xs = [dev(rng.standard_normal((64, T * B)).astype(np.float32)) for _ in range(3)]
+    want = [darb.lstm_layer(dih, dhh, x, H, T, B) for x in xs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    got = []
+    for _ in range(4):
+        got = []
+        for s, x in zip(streams, xs):
+            with torch.cuda.stream(s):
+                got.append(darb.lstm_layer(dih, dhh, x, H, T, B))
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        for a, b in zip(g, w):
+            assert torch.equal(a, b)
+
+
+def test_lstm_layer_under_capture(darb):
+    say("lstm layer captured into a graph, replayed")
+    H, T, B = 128, 16, 8
+    _, (dih, dhh), rng = _lstm_mats(darb, H, 64, np.float16, 4, 64, 0.06, 4)
+    x = dev(rng.standard_normal((64, T * B)).astype(np.float32))
+    want = [host(t) for t in darb.lstm_layer(dih, dhh, x, H, T, B)]
+    h, c = torch.zeros(H, B, device="cuda"), torch.zeros(H, B, device="cuda")
+    seq = torch.empty(H, T * B, device="cuda")
+    ws = torch.empty(darb.lstm_workspace_floats(H, T, B), device="cuda")
+    run = lambda: darb.lstm_layer(dih, dhh, x, H, T, B, h=h, c=c, h_seq=seq,  # noqa: E731
+                                  workspace=ws)
+    run()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run()
+    for _ in range(3):
+        h.zero_()
+        c.zero_()
+        seq.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for t, w in zip((seq, h, c), want):
+            assert np.abs(host(t) - w).max() <= LSTM_TOL
