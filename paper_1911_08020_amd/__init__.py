@@ -129,6 +129,20 @@ def lib():
     return _lib
 
 
+def _load_native():
+    # marshals the per-token calls; links to libdarb.so and to the torch that is loaded
+    try:
+        from . import _darbcall
+    except ImportError as e:
+        raise ImportError(
+            f"DARB call module not built or not loadable ({e}). "
+            "Run `python paper_1911_08020_amd/build.py` first.") from e
+    return _darbcall
+
+
+_native = _load_native()
+
+
 def _strerror(code: int) -> str:
     return _lib.darb_strerror(code).decode()
 
@@ -138,15 +152,22 @@ def _check(rc: int, where: str):
         raise DarbError(rc, where, _lib.darb_last_error().decode())
 
 
+_native.set_check(_check)
+
+
 def _torch():
     import torch
     return torch
 
 
 def _stream_ptr(stream=None):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        # torch.cuda.current_stream() builds a stream object: 2.7 us a call
+        p = _native.current_stream() if _torch().cuda.is_initialized() else None
+        if p is not None:
+            return ctypes.c_void_p(p)
+        stream = _torch().cuda.current_stream()
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def _dtype_code(t) -> int:
@@ -212,6 +233,7 @@ class Plan:
         self.M, self.N, self.nnz = info.M, info.N, info.nnz
         self.workspace_bytes = info.workspace_bytes
         self.packed_words = info.packed_words
+        self._ref = _native.plan_ref(h.value, self.M, self.N, self.nnz, self.packed_words)
         self.bins = [dict(log2b=b.log2b, first_row=b.first_row, rows=b.rows,
                           first_elem=b.first_elem, nblk=b.nblk, first_word=b.first_word)
                      for b in info.bins[:info.nbins]]
@@ -293,6 +315,9 @@ class Plan:
 
     def encode(self, W, values=None, offsets=None, stream=None):
         """BMWM encode of W [M, N] (cuda, fp32/fp16, unit column stride)."""
+        done = _native.encode(self._ref, W, values, offsets, stream)
+        if done is not None:
+            return done
         _require_cuda(W)
         ldw = _row_major_ld(W, self.M, self.N, "W")
         if values is None or offsets is None:
@@ -319,6 +344,9 @@ class Plan:
         return out
 
     def spmv(self, values, offsets, x, y=None, stream=None):
+        done = _native.spmv(self._ref, values, offsets, x, y, stream)
+        if done is not None:
+            return done
         torch = _torch()
         _require_cuda(values, offsets, x)
         self._check_values_offsets(values, offsets)
@@ -329,6 +357,9 @@ class Plan:
         return y
 
     def spmm(self, values, offsets, X, Y=None, stream=None):
+        done = _native.spmm(self._ref, values, offsets, X, Y, stream)
+        if done is not None:
+            return done
         torch = _torch()
         _require_cuda(values, offsets, X)
         self._check_values_offsets(values, offsets)
@@ -368,6 +399,9 @@ class Plan:
         return offsets
 
     def spmv_packed(self, values, packed, x, y=None, stream=None):
+        done = _native.spmv_packed(self._ref, values, packed, x, y, stream)
+        if done is not None:
+            return done
         _require_cuda(values, packed, x)
         self._check_values(values)
         self._check_packed(packed)
@@ -378,6 +412,9 @@ class Plan:
         return y
 
     def spmm_packed(self, values, packed, X, Y=None, stream=None):
+        done = _native.spmm_packed(self._ref, values, packed, X, Y, stream)
+        if done is not None:
+            return done
         _require_cuda(values, packed, X)
         self._check_values(values)
         self._check_packed(packed)
@@ -419,6 +456,9 @@ class Plan:
 
     def spmv_i8(self, codes, scales, x, offsets=None, packed=None, y=None, stream=None):
         """y = diag(scales) (W_i8 x), offsets as bytes or packed words."""
+        done = _native.spmv_i8(self._ref, codes, scales, x, offsets, packed, y, stream)
+        if done is not None:
+            return done
         _require_cuda(codes, scales, x)
         self._check_i8(codes, scales)
         po, pp = self._i8_offsets(offsets, packed)
@@ -429,6 +469,9 @@ class Plan:
 
     def spmm_i8(self, codes, scales, X, offsets=None, packed=None, Y=None, stream=None):
         """Y = diag(scales) (W_i8 X), offsets as bytes or packed words."""
+        done = _native.spmm_i8(self._ref, codes, scales, X, offsets, packed, Y, stream)
+        if done is not None:
+            return done
         _require_cuda(codes, scales, X)
         self._check_i8(codes, scales)
         po, pp = self._i8_offsets(offsets, packed)

@@ -1,4 +1,5 @@
-"""Build the DARB HIP library (libdarb.so) in-tree for gfx950 with hipcc."""
+"""Build the DARB HIP library (libdarb.so) in-tree for gfx950 with hipcc, and the Python call
+module (_darbcall.so) that links to it."""
 import os
 import subprocess
 import sys
@@ -7,8 +8,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdarb.so")
-SOURCES = ["api.cpp", "encode.hip", "product.hip", "product_i8.hip", "lstm_seq.hip",
-           "packed.hip", "prune.hip", "plan.hip", "misc.hip"]
+CALL_MODULE = os.path.join(HERE, "_darbcall.so")
+SOURCES = ["api.cpp", "encode.hip", "product.hip", "product_i8.hip",
+           "lstm_seq.hip", "packed.hip", "prune.hip", "plan.hip", "misc.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -18,8 +20,32 @@ HIPCC_FLAGS = [
 ]
 
 
+def build_call_module(verbose: bool = False) -> str:
+    """Compile the Python call module (csrc/binding.cpp) against libdarb.so and torch."""
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = CALL_MODULE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__",               # the HIP headers ask for it outside hipcc
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(ROOT, "include"), "-isystem", inc,
+           "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           "-L", HERE, "-l:" + os.path.basename(LIB), "-L", libs, "-ltorch_python",
+           "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, CALL_MODULE)
+    return CALL_MODULE
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source to an object (in parallel), then link libdarb.so."""
+    """Compile every source to an object (in parallel), link libdarb.so, then the call module."""
     import shutil
     import tempfile
     from concurrent.futures import ThreadPoolExecutor
@@ -48,6 +74,7 @@ def build(verbose: bool = False) -> str:
         os.replace(tmp, LIB)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
+    build_call_module(verbose)
     return LIB
 
 
