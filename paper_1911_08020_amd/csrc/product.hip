@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
     const int64_t *__restrict__ rowinfo, int64_t H, int64_t batch,
     const float *__restrict__ h_in, const float *__restrict__ U, int64_t ldu,
     float *__restrict__ c, float *__restrict__ h_out, float *__restrict__ h_seq,
-    int64_t ld_seq, int vec_pairs) {
+    int64_t ld_seq) {
     using XL = XLoad<float, CPL>;
     constexpr int L = 1 << LGL;
     constexpr int GM = L >= 16 ? 1 : 16 / L;
@@ -84,8 +84,8 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
         {
             float v[GM];
             int o[GM];
-            PairLoad<Tw, GM, false>::load(values + r0, go, r0, ok ? k : k0, nblk, vec_pairs != 0,
-                                          v, o);
+            using PL = PairLoad<Tw, GM, false, true>;
+            PL::decode(PL::issue(values + r0, go, r0, ok ? k : k0, nblk), go, v, o);
 #pragma unroll
             for (int gi = 0; gi < GM; ++gi) {
                 const bool okg = ok && k + gi < nblk;
@@ -160,16 +160,11 @@ hipError_t launch_lstm_step_t(const darb_plan &whh, int lgl, const void *values,
                               const uint8_t *offsets, int64_t H, int64_t batch, const float *h_in,
                               const float *U, int64_t ldu, float *c, float *h_out, float *h_seq,
                               int64_t ld_seq, hipStream_t st) {
-    const int64_t GM = lgl >= 4 ? 1 : (16 >> lgl);
-    bool vec = GM > 1 && reinterpret_cast<uintptr_t>(values) % (GM * sizeof(Tw)) == 0 &&
-               reinterpret_cast<uintptr_t>(offsets) % GM == 0;
-    for (int g = 0; g < whh.bins.nbins; ++g)
-        vec = vec && whh.bins.nblk[g] % GM == 0 && whh.bins.first_elem[g] % GM == 0;
     const Tw *v = static_cast<const Tw *>(values);
 #define DARB_STEP(LGL)                                                                          \
     hipLaunchKernelGGL((lstm_step_kernel<Tw, CPL, LGL>), dim3(unsigned(H)), dim3(kStepThreads), \
                        0, st, v, offsets, whh.d_rowinfo, H, batch, h_in, U, ldu, c, h_out,       \
-                       h_seq, ld_seq, int(vec))
+                       h_seq, ld_seq)
     switch (lgl) {
         case 0: DARB_STEP(0); break;
         case 1: DARB_STEP(1); break;

@@ -27,7 +27,10 @@
 // and the launch over many waves.  Each wave loads its rows' (value, column)
 // pairs with coalesced loads and broadcasts them across a row's lanes register to
 // register (DPP, swizzle or readlane), gathering X rows kSpmmBatch at a time; the
-// next round's pairs load while this round gathers.  Up to 8 waves split a row group's weights
+// next round's pairs load while this round gathers.  Bound: the gathers' traffic from L2
+// (at B = 64) and the vector instructions beside them (small batches), so an X row costs
+// one 32-bit byte offset, formed once by the lane that loaded the weight, and no test
+// inside a share.  Up to 8 waves split a row group's weights
 // and their partial sums meet in LDS in a fixed order.
 //
 // Both products read the offsets either as one byte per retained weight or in the
@@ -731,7 +734,13 @@ constexpr int kSpmmWaves = kSpmmThreads / kWave;
 constexpr int kSpmmBatch = 8;         // X rows in flight per lane (more waves beat deeper batches)
 constexpr int kRowLanes = 16;         // lanes per row that narrow columns aim at
 
-// CPL consecutive batch columns of one X row, loaded at once (16 bytes when CPL > 1).
+// CPL consecutive batch columns of one X row, loaded at once from any element address
+// (global loads need no alignment on gfx950).
+typedef float f32x4_e __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_e __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32_h __attribute__((aligned(2)));
+typedef uint32_t u32x2_h __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4_h __attribute__((ext_vector_type(4), aligned(2)));
 template <typename Tx, int CPL> struct XLoad;
 template <typename Tx> struct XLoad<Tx, 1> {
     using V = Tx;
@@ -740,22 +749,22 @@ template <typename Tx> struct XLoad<Tx, 1> {
 };
 template <> struct XLoad<float, 4> {
     using V = f32x4;
-    __device__ static V load(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+    __device__ static V load(const float *p) { return *reinterpret_cast<const f32x4_e *>(p); }
     __device__ static float get(const V &v, int i) { return v[i]; }
 };
 template <> struct XLoad<float, 2> {
     using V = f32x2;
-    __device__ static V load(const float *p) { return *reinterpret_cast<const f32x2 *>(p); }
+    __device__ static V load(const float *p) { return *reinterpret_cast<const f32x2_e *>(p); }
     __device__ static float get(const V &v, int i) { return v[i]; }
 };
 template <> struct XLoad<__half, 2> {
     using V = uint32_t;
-    __device__ static V load(const __half *p) { return *reinterpret_cast<const uint32_t *>(p); }
+    __device__ static V load(const __half *p) { return *reinterpret_cast<const u32_h *>(p); }
     __device__ static float get(const V &v, int i) { return half_bits_to_f32(i ? v >> 16 : v); }
 };
 template <> struct XLoad<__half, 4> {
     using V = u32x2;
-    __device__ static V load(const __half *p) { return *reinterpret_cast<const u32x2 *>(p); }
+    __device__ static V load(const __half *p) { return *reinterpret_cast<const u32x2_h *>(p); }
     __device__ static float get(const V &v, int i) {
         const uint32_t w = v[i >> 1];
         return half_bits_to_f32((i & 1) ? (w >> 16) : w);
@@ -763,7 +772,7 @@ template <> struct XLoad<__half, 4> {
 };
 template <> struct XLoad<__half, 8> {
     using V = u32x4;
-    __device__ static V load(const __half *p) { return *reinterpret_cast<const u32x4 *>(p); }
+    __device__ static V load(const __half *p) { return *reinterpret_cast<const u32x4_h *>(p); }
     __device__ static float get(const V &v, int i) {
         const uint32_t w = v[i >> 1];
         return half_bits_to_f32((i & 1) ? (w >> 16) : w);
@@ -799,39 +808,63 @@ template <int LGL, int T> __device__ __forceinline__ int group_bcast(int v) {
     }
 }
 
-// GM consecutive retained weights of a row (values and offsets) for one lane: one
-// vector load each when the bin is aligned for it, element loads otherwise.
-template <typename Tw, int GM, bool PK> struct PairLoad {
-    struct alignas(GM * sizeof(Tw)) VV { Tw e[GM]; };
+// GM consecutive retained weights of a row (values and offsets) for one lane, as a vector
+// load each from any address.  A vector that would pass the end of the format (the last
+// lanes of its last rows) starts `back` slots earlier and is moved down when it is used:
+// one path of loads for all lanes, which the compiler does not take apart.  Packed offsets
+// are one load when the group slot is a multiple of GM (RUNS) and one load per index
+// otherwise.
+template <typename Tw, int GM, bool PK, bool RUNS> struct PairLoad {
+    struct VV { Tw e[GM]; };
     using OV = Off<PK, GM>;
-    // the vector form as loaded, kept in registers while other loads are in flight
-    struct Raw { VV a; typename OV::Raw ob; };
-    // vec: the caller guarantees k % GM == 0, k + GM <= nblk and nblk % GM == 0 (so
-    // the group slot j0 + k is a multiple of GM); otherwise every element index is
-    // clamped into the row [0, nblk).  j0 is the row's first slot in its group.
-    __device__ static Raw issue(const Tw *vr, const GroupOffsets &go, int64_t j0, int k) {
-        return Raw{*reinterpret_cast<const VV *>(vr + k), OV::load(go, j0 + k)};
+    using OS = Off<PK, 1>;
+    static constexpr bool kEach = PK && !RUNS;            // an offset load per index
+    struct Each { typename OS::Raw r[GM]; };
+    // as loaded, kept in registers while other loads are in flight
+    struct Raw {
+        VV a;
+        std::conditional_t<kEach, Each, typename OV::Raw> ob;
+        int back;
+    };
+    // vr: the row's first value, j0 its first slot in the group, left: retained weights from
+    // there to the end of the format (k < left; the format holds at least GM)
+    __device__ static Raw issue(const Tw *vr, const GroupOffsets &go, int64_t j0, int k,
+                                int64_t left) {
+        Raw r;
+        const int64_t past = k + GM - left;
+        r.back = GM > 1 && past > 0 ? int(past) : 0;
+        __builtin_memcpy(&r.a, vr + (k - r.back), sizeof(VV));
+        if constexpr (!PK) {
+            __builtin_memcpy(&r.ob, go.u8 + j0 + (k - r.back), GM);
+        } else if constexpr (kEach) {
+            // (an index past the end of the format: any that can be read)
+#pragma unroll
+            for (int i = 0; i < GM; ++i) r.ob.r[i] = OS::load(go, j0 + (k + i < left ? k + i : k));
+        } else {
+            r.ob = OV::load(go, j0 + k);
+        }
+        return r;
     }
     __device__ static void decode(const Raw &r, const GroupOffsets &go, float (&v)[GM],
                                   int (&o)[GM]) {
-        const typename OV::Bits b = OV::bits(r.ob, go);
 #pragma unroll
-        for (int i = 0; i < GM; ++i) {
-            v[i] = to_f32<Tw>(r.a.e[i]);
-            o[i] = OV::field(b, i, go);
-        }
-    }
-    __device__ static void load(const Tw *vr, const GroupOffsets &go, int64_t j0, int k,
-                                int nblk, bool vec, float (&v)[GM], int (&o)[GM]) {
-        if (vec) {
-            decode(issue(vr, go, j0, k), go, v, o);
+        for (int i = 0; i < GM; ++i) v[i] = to_f32<Tw>(r.a.e[i]);
+        if constexpr (kEach) {
+#pragma unroll
+            for (int i = 0; i < GM; ++i) o[i] = OS::field(OS::bits(r.ob.r[i], go), 0, go);
         } else {
-            using OS = Off<PK, 1>;
+            const typename OV::Bits b = OV::bits(r.ob, go);
 #pragma unroll
-            for (int i = 0; i < GM; ++i) {
-                const int kk = k + i < nblk ? k + i : nblk - 1;
-                v[i] = to_f32<Tw>(vr[kk]);
-                o[i] = OS::field(OS::bits(OS::load(go, j0 + kk), go), 0, go);
+            for (int i = 0; i < GM; ++i) o[i] = OV::field(b, i, go);
+        }
+        if constexpr (GM > 1) {
+            for (int back = r.back; __any(back > 0); --back) {   // wave-uniform, rarely
+                const bool move = back > 0;
+#pragma unroll
+                for (int i = 0; i + 1 < GM; ++i) {
+                    v[i] = move ? v[i + 1] : v[i];
+                    if constexpr (!PK) o[i] = move ? o[i + 1] : o[i];
+                }
             }
         }
     }
@@ -843,19 +876,23 @@ template <typename Tw, int GM, bool PK> struct PairLoad {
 // of a row load S = max(2^LGL, 16) of the row's (value, column) pairs per step, one
 // pair per lane and group, straight from HBM with coalesced loads, then broadcast
 // each pair to the row's lanes with a register-to-register exchange and gather its
-// X row; kSpmmBatch gathers are in flight per lane.  With aligned pairs the loads
-// are software pipelined: a round's pairs are issued right after the previous
-// round's last gathers, so their HBM latency overlaps those gathers.  Partial sums
+// X row; kSpmmBatch gathers are in flight per lane.  The loads are software pipelined: a
+// round's pairs are issued right after the previous round's last gathers, so their HBM
+// latency overlaps those gathers, whatever the rows' length and alignment (a path of
+// element loads for rows that are no multiple of GM weights waited for each round: 6000
+// columns fp32, batch 5, 17.2 us against 11.2).  With 64-bit addresses and a test per gather before:
+// 4608 x 3072 fp16, batch 16, 10.8 -> 7.7 us; 6000 x 1500 fp32 packed, batch 20, 9.7 -> 8.2;
+// 4096 x 9216 fp32, batch 64, 21.6 -> 20.2.  Partial sums
 // of the KS waves meet in LDS (`part`, kSpmmThreads * CPL floats) in a fixed order.
 // The finished rows go to
 //     epi(row_ok, col_ok, original row, first column, acc[CPL], lane in row),
 // called by every lane of the waves that hold finished rows (wave-uniform), so an
 // epilogue may exchange values between the lanes of a row.
-template <typename Tw, typename Tx, int CPL, int LGL, bool PK, typename Epi>
+template <typename Tw, typename Tx, int CPL, int LGL, bool PK, bool WIDE, typename Epi>
 __device__ __forceinline__ void spmm_tile(
     int tile, const Tw *__restrict__ values, const void *__restrict__ offs,
     const Tx *__restrict__ X, int64_t ldx, int64_t B, const int32_t *__restrict__ perm, int N,
-    const BinTable &bins, const ProductSchedule &sch, float *part, Epi &&epi) {
+    const BinTable &bins, const ProductSchedule &sch, int64_t nnz, float *part, Epi &&epi) {
     using XL = XLoad<Tx, CPL>;
     constexpr int L = 1 << LGL;
     constexpr int R = kWave >> LGL;                       // rows per wave
@@ -893,9 +930,12 @@ __device__ __forceinline__ void spmm_tile(
     const int rl = rg * R + (lane >> LGL);                // row of this lane in the block
     const bool row_ok = rl < rows_here;
     const int sub = lane & (L - 1);
-    const int64_t col0 = (int64_t(slab) * L + sub) * CPL;
-    const bool col_ok = col0 < B;                         // CPL > 1 only when CPL divides B
-    const int64_t col_c = col_ok ? col0 : 0;
+    int64_t col0 = (int64_t(slab) * L + sub) * CPL;
+    const bool col_ok = col0 < B;
+    // CPL <= B; where it does not divide B the last columns belong to two lanes, which
+    // compute and store the same
+    col0 = col0 + CPL <= B ? col0 : B - CPL;
+    const int64_t col_c = col0;
     // each wave's share is a multiple of 16 weights (of GM, so a lane's GM-vector of
     // weights is either entirely inside [kbeg, kend) or entirely outside); the split
     // points do not depend on the lanes per row, so neither do the sums
@@ -904,75 +944,92 @@ __device__ __forceinline__ void spmm_tile(
     const int kend = kbeg + share < nblk ? kbeg + share : nblk;
     const int64_t j0 = (row0 + (row_ok ? rl : 0)) * nblk;   // the row's first slot in its group
     const Tw *vr = values + first_elem + j0;
+    const int64_t left = nnz - first_elem - j0;           // retained weights from the row on
     const GroupOffsets go = group_offsets(offs, bins, g);
 
     float acc[CPL];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) acc[q] = 0.0f;
 
-    const bool vec_pairs = pick(sch.vec, g) != 0;
-    using PL = PairLoad<Tw, GM, PK>;
-    // a round's pairs (DEPTH steps) as values and clamped columns; -1 marks no weight
+    // a round's pairs (DEPTH steps) as values and the X rows they select: each weight's
+    // byte offset into X, formed once by the lane that loaded it (WIDE, X past 4 GiB: its
+    // column); weights past the share select row 0 and are left out below
+    const uint32_t ldb = WIDE ? 1u : uint32_t(ldx) * uint32_t(sizeof(Tx));
     auto settle = [&](int k0, int st, const float (&v)[GM], const int (&o)[GM],
-                      float (&vl)[DEPTH][GM], int (&cl)[DEPTH][GM]) {
+                      float (&vl)[DEPTH][GM], uint32_t (&cl)[DEPTH][GM]) {
         const int k = k0 + st * S + sub * GM;
         const bool ok = row_ok && k < kend;
 #pragma unroll
         for (int gi = 0; gi < GM; ++gi) {
             const bool okg = ok && k + gi < kend;         // element test for the scalar path
-            vl[st][gi] = okg ? v[gi] : 0.0f;
-            const int c = ((k + gi) << lb) + o[gi];
-            cl[st][gi] = okg ? (c < N ? c : N - 1) : -1;   // the encode gives c < N
-        }
-    };
-    // vector pair loads of the round at k0 (lanes past the share or the rows load a
-    // valid slot of their row block and are masked when settled)
-    auto issue_round = [&](int k0, typename PL::Raw (&raw)[DEPTH]) {
-#pragma unroll
-        for (int st = 0; st < DEPTH; ++st) {
-            const int k = k0 + st * S + sub * GM;
-            raw[st] = PL::issue(vr, go, j0, row_ok && k < kend ? k : kbeg);
+            vl[st][gi] = v[gi];
+            int c = ((k + gi) << lb) + o[gi];
+            c = c < N ? c : N - 1;                        // the encode gives c < N
+            c = okg ? c : 0;
+            cl[st][gi] = uint32_t(c) * ldb;
         }
     };
     // gathers of one round (DEPTH steps of S weights), NB X rows in flight per lane;
     // `after` runs right after the round's last gathers are issued (the next round's
-    // pair loads go there, so they overlap these gathers without delaying their use)
-    auto gather_round = [&](int k0, const float (&vl)[DEPTH][GM], const int (&cl)[DEPTH][GM],
+    // pair loads go there, so they overlap these gathers without delaying their use).
+    // Rows of a group are equally long, so whether a weight lies inside the share is the
+    // same for the whole wave: a batch inside it needs no test.  Lanes without a row or a
+    // column sum something finite or not that nobody reads.
+    const uint32_t colb = uint32_t(col_c) * uint32_t(sizeof(Tx));
+    auto gather_round = [&](int k0, const float (&vl)[DEPTH][GM], const uint32_t (&cl)[DEPTH][GM],
                             auto &&after) {
         static_for<0, T / NB>([&](auto bc) {
             constexpr int b0 = decltype(bc)::value * NB;
-            if (k0 + (b0 / S) * S >= kend) return;         // wave-uniform: past the share
-            float vv[NB];
-            int cc[NB];
+            if (k0 + b0 >= kend) return;                   // wave-uniform: past the share
             typename XL::V xv[NB];
             static_for<0, NB>([&](auto uc) {
                 constexpr int f = b0 + decltype(uc)::value;   // weight k0 + f of the round
                 constexpr int st = f / S, fs = f % S;
-                vv[f - b0] = __builtin_bit_cast(
-                    float, group_bcast<LGL, fs / GM>(__builtin_bit_cast(int, vl[st][fs % GM])));
-                cc[f - b0] = group_bcast<LGL, fs / GM>(cl[st][fs % GM]);
-                const int64_t c = cc[f - b0] >= 0 ? cc[f - b0] : 0;
-                xv[f - b0] = XL::load(X + c * ldx + col_c);
+                const uint32_t row =
+                    uint32_t(group_bcast<LGL, fs / GM>(int(cl[st][fs % GM])));
+                if constexpr (WIDE)
+                    xv[f - b0] = XL::load(X + int64_t(row) * ldx + col_c);
+                else
+                    xv[f - b0] = XL::load(reinterpret_cast<const Tx *>(
+                        reinterpret_cast<const char *>(X) + (row + colb)));
             });
             if constexpr (b0 + NB == T) after();
+            auto add = [&](auto uc) {
+                constexpr int f = b0 + decltype(uc)::value;
+                constexpr int st = f / S, fs = f % S;
+                const float w = __builtin_bit_cast(
+                    float, group_bcast<LGL, fs / GM>(__builtin_bit_cast(int, vl[st][fs % GM])));
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                if (cc[u] >= 0 && col_ok) {
-#pragma unroll
-                    for (int q = 0; q < CPL; ++q)
-                        acc[q] = fmaf(vv[u], XL::get(xv[u], q), acc[q]);
-                }
+                for (int q = 0; q < CPL; ++q)
+                    acc[q] = fmaf(w, XL::get(xv[f - b0], q), acc[q]);
+            };
+            if (k0 + b0 + NB <= kend) {                    // wave-uniform
+                static_for<0, NB>(add);
+            } else {
+                static_for<0, NB>([&](auto uc) {
+                    if (k0 + b0 + int(decltype(uc)::value) < kend) add(uc);
+                });
             }
         });
     };
 
-    if (vec_pairs) {
-        // software pipelined: the pairs of round i + 1 load while round i gathers
+    // software pipelined: the pairs of round i + 1 load while round i gathers
+    auto run = [&](auto runs) {
+        using PL = PairLoad<Tw, GM, PK, decltype(runs)::value>;
         typename PL::Raw raw[DEPTH];
-        if (kbeg < kend) issue_round(kbeg, raw);          // wave-uniform
+        // lanes past the share or the rows load a slot of their row block that exists and
+        // are masked when settled
+        auto issue_round = [&](int k0) {
+#pragma unroll
+            for (int st = 0; st < DEPTH; ++st) {
+                const int k = k0 + st * S + sub * GM;
+                raw[st] = PL::issue(vr, go, j0, row_ok && k < kend ? k : kbeg, left);
+            }
+        };
+        if (kbeg < kend) issue_round(kbeg);               // wave-uniform
         for (int k0 = kbeg; k0 < kend; k0 += DEPTH * S) {
             float vl[DEPTH][GM];
-            int cl[DEPTH][GM];
+            uint32_t cl[DEPTH][GM];
 #pragma unroll
             for (int st = 0; st < DEPTH; ++st) {
                 float v[GM];
@@ -982,23 +1039,15 @@ __device__ __forceinline__ void spmm_tile(
             }
             const int k1 = k0 + DEPTH * S;
             gather_round(k0, vl, cl, [&] {
-                if (k1 < kend) issue_round(k1, raw);      // wave-uniform
+                if (k1 < kend) issue_round(k1);           // wave-uniform
             });
         }
+    };
+    if constexpr (PK && GM > 1) {
+        if (pick(sch.vec, g) != 0) run(std::true_type{});
+        else run(std::false_type{});
     } else {
-        for (int k0 = kbeg; k0 < kend; k0 += DEPTH * S) {
-            float vl[DEPTH][GM];
-            int cl[DEPTH][GM];
-#pragma unroll
-            for (int st = 0; st < DEPTH; ++st) {
-                const int k = k0 + st * S + sub * GM;
-                float v[GM];
-                int o[GM];
-                PL::load(vr, go, j0, row_ok && k < kend ? k : kbeg, nblk, false, v, o);
-                settle(k0, st, v, o, vl, cl);
-            }
-            gather_round(k0, vl, cl, [] {});
-        }
+        run(std::true_type{});
     }
 
     // combine the KS partial sums of each row group in a fixed order
@@ -1017,15 +1066,15 @@ __device__ __forceinline__ void spmm_tile(
     if (ks == 0) epi(row_ok, col_ok, row_ok ? perm[first_row + row0 + rl] : 0, col0, acc, sub);
 }
 
-template <typename Tw, typename Tx, int CPL, int LGL, bool PK>
+template <typename Tw, typename Tx, int CPL, int LGL, bool PK, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads) void spmm_kernel(
     const Tw *__restrict__ values, const void *__restrict__ offs,
     const Tx *__restrict__ X, int64_t ldx, int64_t B, float *__restrict__ Y, int64_t ldy,
     const int32_t *__restrict__ perm, int N, BinTable bins, ProductSchedule sch,
-    const float *__restrict__ scales) {
+    const float *__restrict__ scales, int64_t nnz) {
     __shared__ float part[kSpmmThreads * CPL];
-    spmm_tile<Tw, Tx, CPL, LGL, PK>(
-        int(blockIdx.x), values, offs, X, ldx, B, perm, N, bins, sch, part,
+    spmm_tile<Tw, Tx, CPL, LGL, PK, WIDE>(
+        int(blockIdx.x), values, offs, X, ldx, B, perm, N, bins, sch, nnz, part,
         [&](bool row_ok, bool col_ok, int32_t orig, int64_t col0, const float (&acc)[CPL], int) {
             if (row_ok && col_ok) {
                 const float sc = kScaled<Tw> ? scales[orig] : 1.0f;
@@ -1462,12 +1511,13 @@ hipError_t launch_spmv_form(const darb_plan &p, const void *values, const uint8_
     return launch_spmv_t<Tw, Tx, true>(p, values, nullptr, packed, x, y, scales, st);
 }
 
-inline bool spmm_schedule(const darb_plan &p, int64_t B, int cpl, size_t wbytes,
-                          const void *values, const uint8_t *offsets, ProductSchedule &s) {
+inline bool spmm_schedule(const darb_plan &p, int64_t B, int cpl, ProductSchedule &s,
+                          bool wide = false) {
     s = ProductSchedule{};
     s.nbins = p.bins.nbins;
     const int64_t lanes = (B + cpl - 1) / cpl;        // lanes needed for all columns
-    const int lgL = lanes >= kWave ? 6 : ilog2_ceil(lanes);
+    int lgL = wide || lanes >= kWave ? 6 : ilog2_ceil(lanes);
+    if (p.nnz < 16 && lgL < 4) lgL = 4;               // no room for vectors of weights
     const int64_t slabs = (lanes + (int64_t(1) << lgL) - 1) >> lgL;
     if (slabs > 0x7FFFFFFF) return false;
     s.col_slabs = int32_t(slabs);
@@ -1483,11 +1533,9 @@ inline bool spmm_schedule(const darb_plan &p, int64_t B, int cpl, size_t wbytes,
         const int rows_pb = R * (kSpmmWaves / KS);
         s.log2_lanes[g] = lgL;
         s.ksplit[g] = KS;
-        // pairs load as GM-element vectors when every lane's run is aligned for it
+        // a lane's packed offsets are one load when every row's slots are whole runs of GM
         const int64_t GM = lgL >= 4 ? 1 : (16 >> lgL);
-        s.vec[g] = (GM > 1 && nblk % GM == 0 && p.bins.first_elem[g] % GM == 0 &&
-                    reinterpret_cast<uintptr_t>(values) % (GM * wbytes) == 0 &&
-                    offsets_aligned(offsets, int(GM))) ? 1 : 0;
+        s.vec[g] = nblk % GM == 0;
         s.block_begin[g] = int32_t(blocks);
         blocks += (p.bins.rows[g] + rows_pb - 1) / rows_pb * slabs;
         if (blocks > 0x7FFFFFFF) return false;
@@ -1508,8 +1556,9 @@ hipError_t launch_spmm_cpl(const darb_plan &p, const ProductSchedule &s, const T
     constexpr bool kEvery = CPL == 1 || CPL * int(sizeof(Tx)) == 16;
     if (!kEvery && lgl < 4) return hipErrorInvalidConfiguration;
 #define DARB_SPMM(LGL)                                                                    \
-    hipLaunchKernelGGL((spmm_kernel<Tw, Tx, CPL, LGL, PK>), dim3(blocks), dim3(kSpmmThreads), \
-                       0, st, v, offs, x, ldx, B, Y, ldy, p.d_perm, N, p.bins, s, scales)
+    hipLaunchKernelGGL((spmm_kernel<Tw, Tx, CPL, LGL, PK, false>), dim3(blocks), dim3(kSpmmThreads), \
+                       0, st, v, offs, x, ldx, B, Y, ldy, p.d_perm, N, p.bins, s, scales,  \
+                       p.nnz)
     switch (lgl) {
         case 0: if constexpr (kEvery) DARB_SPMM(0); break;
         case 1: if constexpr (kEvery) DARB_SPMM(1); break;
@@ -1550,7 +1599,7 @@ hipError_t launch_spmm_t(const darb_plan &p, const void *values, const uint8_t *
                 lgl = -1;
         if (lgl >= 0) {
             ProductSchedule s;
-            if (!spmm_schedule(p, B, CPL, sizeof(Tw), values, offsets, s))
+            if (!spmm_schedule(p, B, CPL, s))
                 return hipErrorInvalidConfiguration;
             const int64_t slabs = (B + (int64_t(4) << lgl) - 1) / (int64_t(4) << lgl);
             if (slabs > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
@@ -1578,27 +1627,46 @@ hipError_t launch_spmm_t(const darb_plan &p, const void *values, const uint8_t *
     }
     // columns per lane: 16 bytes of X when that leaves a row at least 5 lanes (a
     // group of 8); for smaller batches the fewest columns that keep a row within 16
-    // lanes, so the launch still has many waves.  The width must divide B and keep
-    // the loads aligned.  (Measured: 16-byte loads on 8 lanes beat 8-byte loads on 16;
-    // rows of 2 or 4 lanes leave too few waves.)
-    auto fits = [&](int c) {
-        const int64_t bytes = int64_t(c) * int64_t(sizeof(Tx));
-        return B % c == 0 && reinterpret_cast<uintptr_t>(X) % bytes == 0 &&
-               (ldx * int64_t(sizeof(Tx))) % bytes == 0;
-    };
+    // lanes, so the launch still has many waves.  (Measured: 16-byte loads on 8 lanes beat
+    // 8-byte loads on 16; rows of 2 or 4 lanes leave too few waves.)  The loads take any
+    // 4-byte aligned address and the last lane any remainder (fp16 rows an odd number of
+    // elements apart load by element: 2-byte aligned vectors are slower).  Where the batch
+    // is no multiple, a column per lane spreads a row over more lanes: better for few rows
+    // (512 x 9216 fp32, batch 33: 14.3 us against 20.7), worse from 16 waves per CU on
+    // (8192 x 3072: 36.9 against 19.5).
+    const bool dwords = reinterpret_cast<uintptr_t>(X) % 4 == 0 &&
+                        (ldx * int64_t(sizeof(Tx))) % 4 == 0;
+    const int64_t vec_lanes = int64_t(1) << ilog2_ceil((B + CPL - 1) / CPL);
+    const bool many = p.M * (vec_lanes < kWave ? vec_lanes : int64_t(kWave)) / kWave * kSpmmWaves >=
+                      16 * (p.cus > 0 ? p.cus : 256);
     int cpl = 1;
-    if ((B + CPL - 1) / CPL > 4 && fits(CPL)) {
-        cpl = CPL;
-    } else {
-        while (cpl < CPL && (B + cpl - 1) / cpl > kRowLanes && fits(2 * cpl)) cpl *= 2;
+    if (dwords || sizeof(Tx) == 4) {
+        if ((B + CPL - 1) / CPL > 4 && (B % CPL == 0 || many)) {
+            cpl = CPL;
+        } else {
+            while (cpl < CPL && (B + cpl - 1) / cpl > kRowLanes &&
+                   (B % (2 * cpl) == 0 || many))
+                cpl *= 2;
+        }
     }
+    // the gathers address X with 32-bit byte offsets; past 4 GiB a lane per column and 64
+    // lanes per row with 64-bit addresses, which gives the same sums
+    const int64_t most = int64_t(0xFFFFFFFF) / int64_t(sizeof(Tx));
+    const bool wide = ldx > most || (p.N - 1) * ldx + B > most;
+    if (wide) cpl = 1;
     ProductSchedule s;
-    if (!spmm_schedule(p, B, cpl, sizeof(Tw), values, offsets, s))
+    if (!spmm_schedule(p, B, cpl, s, wide))
         return hipErrorInvalidConfiguration;
     if (s.block_begin[s.nbins] == 0) return hipSuccess;
     const Tw *v = static_cast<const Tw *>(values);
     const void *offs = offset_source(p, offsets, packed);
     const Tx *x = static_cast<const Tx *>(X);
+    if (wide) {
+        hipLaunchKernelGGL((spmm_kernel<Tw, Tx, 1, 6, PK, true>), dim3(s.block_begin[s.nbins]),
+                           dim3(kSpmmThreads), 0, st, v, offs, x, ldx, B, Y, ldy, p.d_perm,
+                           int(p.N), p.bins, s, scales, p.nnz);
+        return hipGetLastError();
+    }
     if (cpl == 1)
         return launch_spmm_cpl<Tw, Tx, 1, PK>(p, s, v, offs, B, x, ldx, Y, ldy, scales, st);
     if (cpl == 2)
