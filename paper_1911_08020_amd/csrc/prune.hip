@@ -19,7 +19,7 @@
 // order, which for row counts means rows in ascending order (by the count pass's
 // last workgroup, only when some keys equal to t are not kept).
 //
-// From 64 MiB of W one pass streams all of W.  A sample of W (about 1/32) first
+// From 5 Mi elements one pass streams all of W.  A sample of W (about 1/32) first
 // histograms finer first digits (the key's top 14 bits for fp32, 11 for fp16; the
 // same launch resets the state, and the count pass leaves the sample's histogram
 // at zero for the next call on the workspace), from
@@ -38,12 +38,17 @@
 // passes stream W from the first digit on instead (the result is the same).  When
 // the sample predicts more candidates than half the room, the split pass takes the
 // exact first-digit histogram of W instead, and the later passes stream W for the
-// remaining digits.  The host launches as many passes after the split as the
-// key's digits need; a pass with nothing left to choose hands the state on.  Below
-// 64 MiB of W there is no sample and no split: a reset launch, then every pass
-// streams W, which there costs less than the extra launches.  A pass over the candidates runs only the
-// workgroups they fill.  All state stays on the device; nothing returns to the host
-// between passes.
+// remaining digits.  The split pass also counts the candidates' first digit while it
+// has them (a few hundred per workgroup, added to an LDS histogram), so the pass after
+// it starts at the second: 4096 x 9216 fp32 59.7 -> 57.2 us.  The host launches as many
+// passes after the split as the key's digits need; a pass with nothing left to choose
+// hands the state on.  Below 5 Mi elements there is no sample and no split: a reset
+// launch, then every pass streams W, which there costs less than the extra launches.  A
+// pass over the candidates runs only the workgroups they fill.  All state stays on the
+// device; nothing returns to the host between passes.
+//
+// Rows start at any element address: every 16-byte vector inside a row is one load
+// (6000 x 2001 fp32: 106 -> 59 us, half of it from the loads).
 #include <algorithm>
 
 #include <mutex>
@@ -120,10 +125,22 @@ constexpr int kSplitLds = 8192;                     // candidates a workgroup ca
 constexpr int kWaveRoom = kSplitLds / kHistWaves;   // of which each of its waves' own
 constexpr int64_t kSampleEvery = 32;                // the sample reads about 1/32 of W
 constexpr int64_t kSampleDrift = 37;                // vectors added to the sample stride
-constexpr int64_t kSampleChunk = 4;                 // vectors per lane in one sampled range
+// The sample is taken in pieces of 16 vectors (256 bytes), so that nearly every row gives
+// its share of it: rows differ in density (that is what DARB adapts to), and ranges of
+// 4 KiB from an eighth of the rows missed the threshold by more than the margin every
+// second time on 8192 x 4096, where a miss costs four passes over W (170 us instead of
+// 60).
+constexpr int kPieceLanes = 16;
+constexpr int kSampleLoads = 4;                     // vectors in flight per thread
 constexpr int kSampleGroups = 256;                  // workgroups of the sample pass
 constexpr int kCandPerThread = 8;                   // candidate passes: keys per thread
-constexpr int64_t kSplitMinBytes = int64_t(64) << 20;   // W size from which the split pays
+// Elements of W from which the split pays: 2048 x 2048 fp32 takes 41.0 us without it and
+// 43.3 with it, 4096 x 2048 47.8 and 43.2, 4096 x 4096 fp16 53.7 and 47.4.
+constexpr int64_t kSplitMinElems = int64_t(5) << 20;
+// Bytes of W from which the sample resets the state itself (and relies on the last call
+// for a zero histogram); below, the reset is a launch of its own, since a fresh workspace
+// would cost more than it: passes over W instead of candidates.
+constexpr int64_t kResetInSample = int64_t(64) << 20;
 
 template <typename Bits> struct PruneTraits;
 template <> struct PruneTraits<uint32_t> {
@@ -145,12 +162,21 @@ constexpr int kFineBins = 1 << 14;
 
 template <typename Bits, int VEC> struct alignas(16) PVec { Bits e[VEC]; };
 
+// 16 bytes of a row at any element address: global loads need no alignment on gfx950, so
+// rows that do not start on 16 bytes (an odd N, an offset view) still take one load
+// instruction per vector.
+template <typename Bits> struct RowVec;
+template <> struct RowVec<uint32_t> {
+    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <> struct RowVec<uint16_t> {
+    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(2)));
+};
+
 // Work is split evenly over the waves: W is taken as M rows padded to whole
 // VEC-element vectors, flattened, and wave w streams elements [w * per_wave,
 // (w + 1) * per_wave) of that (per_wave a multiple of kWave * VEC, so every piece
-// starts on a vector boundary), in pieces of one row each.  A sample reads ranges
-// of per_wave elements range_stride apart instead (range_stride = per_wave reads
-// all of W).
+// starts on a vector boundary), in pieces of one row each.
 template <typename Bits> constexpr int64_t round_width() {
     return int64_t(PruneTraits<Bits>::UNROLL) * kWave * PruneTraits<Bits>::VEC;
 }
@@ -162,10 +188,10 @@ template <typename Bits> __host__ __device__ constexpr int64_t padded_n(int64_t 
 // (all lanes together), then round(keys, valid) for every round of the piece
 // (all lanes together): the lane's kUnroll * VEC keys and a mask of those inside
 // the row.
-template <typename Bits, bool ALIGNED, typename U, typename R>
+template <typename Bits, typename U, typename R>
 __device__ __forceinline__ void for_each_round(const Bits *__restrict__ W, int64_t ldw,
                                                int64_t M, int64_t N, int64_t per_wave,
-                                               int64_t range_stride, U &&on_unit, R &&round) {
+                                               U &&on_unit, R &&round) {
     using Tr = PruneTraits<Bits>;
     constexpr int VEC = Tr::VEC;
     constexpr int kUnroll = Tr::UNROLL;
@@ -177,7 +203,7 @@ __device__ __forceinline__ void for_each_round(const Bits *__restrict__ W, int64
     const int64_t tw = int64_t(gridDim.x) * (blockDim.x / kWave);
     const int64_t Np = padded_n<Bits>(N);
     const int64_t total = M * Np;
-    for (int64_t a = gw * range_stride; a < total; a += tw * range_stride) {   // wave-uniform
+    for (int64_t a = gw * per_wave; a < total; a += tw * per_wave) {   // wave-uniform
         const int64_t b = a + per_wave < total ? a + per_wave : total;
         int64_t r = a / Np;
         int64_t c = a - r * Np;
@@ -198,10 +224,10 @@ __device__ __forceinline__ void for_each_round(const Bits *__restrict__ W, int64
                     if (cc >= c_end) {
                         v[q] = PVec<Bits, VEC>{};
                         valid[q] = 0;
-                    } else if (ALIGNED && cc + VEC <= c_end) {
-                        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                        const u32x4 t = __builtin_nontemporal_load(
-                            reinterpret_cast<const u32x4 *>(row + cc));
+                    } else if (cc + VEC <= c_end) {
+                        typedef typename RowVec<Bits>::T RV;
+                        const RV t = __builtin_nontemporal_load(
+                            reinterpret_cast<const RV *>(row + cc));
                         v[q] = __builtin_bit_cast(PVec<Bits, VEC>, t);
                         valid[q] = (1u << VEC) - 1u;
                     } else {
@@ -300,17 +326,16 @@ __device__ __forceinline__ void for_each_round_halves(const Bits *__restrict__ W
 }
 
 // As for_each_round, with f(key) for every element inside the row (per lane).
-template <typename Bits, bool ALIGNED, typename U, typename F>
+template <typename Bits, typename U, typename F>
 __device__ __forceinline__ void for_each_key(const Bits *__restrict__ W, int64_t ldw, int64_t M,
-                                             int64_t N, int64_t per_wave, int64_t range_stride,
-                                             U &&on_unit, F &&f) {
+                                             int64_t N, int64_t per_wave, U &&on_unit, F &&f) {
     constexpr int K = PruneTraits<Bits>::UNROLL * PruneTraits<Bits>::VEC;
-    for_each_round<Bits, ALIGNED>(W, ldw, M, N, per_wave, range_stride, on_unit,
-                                  [&](const uint32_t (&keys)[K], uint32_t mask) {
+    for_each_round<Bits>(W, ldw, M, N, per_wave, on_unit,
+                         [&](const uint32_t (&keys)[K], uint32_t mask) {
 #pragma unroll
-                                      for (int j = 0; j < K; ++j)
-                                          if (mask & (1u << j)) f(keys[j]);
-                                  });
+                             for (int j = 0; j < K; ++j)
+                                 if (mask & (1u << j)) f(keys[j]);
+                         });
 }
 
 // Block-wide inclusive scan of one value per thread (kHistThreads threads).
@@ -359,24 +384,14 @@ struct ResolveLds {
     uint32_t d[4];
 };
 
-// The pass the state slot describes, with its pending digit chosen: the digit d of
-// the pending histogram where the count of matching keys with digit > d is < k_rem
-// <= that count plus total[d] is appended to the prefix.  Every workgroup of the
-// kernel does the same from the same totals, which the previous kernel completed
-// (plain loads suffice after the kernel boundary).
-__device__ __forceinline__ Pass resolve(const PruneState *__restrict__ S,
-                                        const unsigned long long *__restrict__ totals,
-                                        int key_bits, ResolveLds &L) {
-    Pass P;
-    P.prefix = S->prefix;
-    P.hi = S->hi < uint32_t(key_bits) ? S->hi : uint32_t(key_bits);
-    P.base = S->base;
-    P.cand = S->from_cand != 0;
-    P.k_rem = S->k_rem;
-    P.n_last = S->n_last;
-    const uint32_t width = S->pend_width < P.hi ? S->pend_width : P.hi;
-    if (width == 0) return P;                           // uniform
-    const unsigned long long *t = totals + size_t(S->pend_buf % kTotalsBuffers) * kDigitBins;
+// Pass P with its pending digit of `width` bits (> 0) chosen from the histogram t: the
+// digit d where the count of matching keys with digit > d is < k_rem <= that count plus
+// t[d] is appended to the prefix.  Every workgroup of the kernel does the same from the
+// same totals, which the previous kernel completed (plain loads suffice after the
+// kernel boundary).
+__device__ __forceinline__ Pass choose_digit(Pass P, uint32_t width,
+                                             const unsigned long long *__restrict__ t,
+                                             ResolveLds &L) {
     const int bins = 1 << width;
     for (int b = int(threadIdx.x); b < bins; b += kHistThreads) L.tot[b] = t[b];
     if (threadIdx.x == 0) {                             // if no digit qualifies
@@ -404,6 +419,22 @@ __device__ __forceinline__ Pass resolve(const PruneState *__restrict__ S,
     P.k_rem = int64_t(L.v[1]);
     P.n_last = L.v[2];
     return P;
+}
+
+// The pass the state slot describes, with its pending digit (if any) chosen.
+__device__ __forceinline__ Pass resolve(const PruneState *__restrict__ S,
+                                        const unsigned long long *__restrict__ totals,
+                                        int key_bits, ResolveLds &L) {
+    Pass P;
+    P.prefix = S->prefix;
+    P.hi = S->hi < uint32_t(key_bits) ? S->hi : uint32_t(key_bits);
+    P.base = S->base;
+    P.cand = S->from_cand != 0;
+    P.k_rem = S->k_rem;
+    P.n_last = S->n_last;
+    const uint32_t width = S->pend_width < P.hi ? S->pend_width : P.hi;
+    if (width == 0) return P;                           // uniform
+    return choose_digit(P, width, totals + size_t(S->pend_buf % kTotalsBuffers) * kDigitBins, L);
 }
 
 // The split pass's bracket [dlo, dhi] of fine first digits (the top FB bits of the
@@ -509,10 +540,17 @@ enum HistRole {
                           // hold the threshold, else from W (from the first digit on)
 };
 
+// Low bits of a candidate's key relative to the lowest key of the bracket [dlo, dhi].
+template <typename Bits>
+__device__ __forceinline__ uint32_t bracket_bits(uint32_t dlo, uint32_t dhi) {
+    return uint32_t(PruneTraits<Bits>::KEY_BITS - PruneTraits<Bits>::SAMPLE_BITS) +
+           bit_length(dhi - dlo);
+}
+
 // The pass after a split pass that kept the sample's bracket: over the candidates'
 // keys relative to the bracket's lowest key when G < k <= G + candidates (G the
-// keys above the bracket), else over all of W from the first digit.  `cap` bounds
-// the candidate count read back.
+// keys above the bracket; the split pass has counted their first digit), else over all
+// of W from the first digit.  `cap` bounds the candidate count read back.
 template <typename Bits>
 __device__ __forceinline__ Pass pass_after_split(const SplitInfo *__restrict__ I, int64_t k,
                                                  uint64_t cap) {
@@ -525,7 +563,7 @@ __device__ __forceinline__ Pass pass_after_split(const SplitInfo *__restrict__ I
     P.n_last = 0;
     if (!I->overflow && n <= cap && dlo <= dhi && G < kk && kk <= G + n) {
         P.base = dlo << first_shift;
-        P.hi = uint32_t(first_shift) + bit_length(dhi - dlo);
+        P.hi = bracket_bits<Bits>(dlo, dhi);
         P.cand = true;
         P.k_rem = int64_t(kk - G);
     } else {
@@ -568,7 +606,7 @@ __device__ __forceinline__ void hand_on(PruneState *__restrict__ out, const Pass
 // they fill take part, and their keys are loaded before the pending digit is
 // chosen (one memory latency for both).  A pass that would find every bit chosen
 // once the pending digit is leaves that digit to the count and hands the state on.
-template <typename Bits, bool ALIGNED>
+template <typename Bits>
 __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
     const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t per_wave,
     PruneState *__restrict__ slots, const SplitInfo *__restrict__ info,
@@ -582,9 +620,18 @@ __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
     const bool derived = role == kRoleAfterSplit && info->single;   // uniform
     Pass P;
     bool from_cand;
+    uint32_t split_width = 0;                           // the candidates' first digit, counted
     if (derived) {
         P = pass_after_split<Bits>(info, k, cap);
         from_cand = P.cand;
+        if (from_cand) {
+            split_width = uint32_t(digit_width(int(P.hi)));
+            if (P.hi == split_width) {                  // which is the only one
+                if (blockIdx.x == 0 && threadIdx.x == 0)
+                    hand_on(slots + (rd ^ 1), P, int(split_width), kBufSplit);
+                return;
+            }
+        }
     } else {
         const uint32_t hi = S->hi < uint32_t(KB) ? S->hi : uint32_t(KB);
         if (hi <= S->pend_width) {                      // nothing after the pending digit
@@ -617,6 +664,8 @@ __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
     if (from_cand) load_batch();
     asm volatile("" ::: "memory");                      // the loads go out first
     if (!derived) P = resolve(S, totals, KB, L);
+    else if (split_width)
+        P = choose_digit(P, split_width, totals + size_t(kBufSplit) * kDigitBins, L);
     const int width = digit_width(int(P.hi));
     if (blockIdx.x == 0 && threadIdx.x == 0) hand_on(slots + (rd ^ 1), P, width, buf);
     const int bins = 1 << width;
@@ -640,7 +689,7 @@ __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
             if (i0 < n) load_batch();
         }
     } else {
-        for_each_key<Bits, ALIGNED>(W, ldw, M, N, per_wave, per_wave, [](int64_t) {}, add);
+        for_each_key<Bits>(W, ldw, M, N, per_wave, [](int64_t) {}, add);
     }
     __syncthreads();
     unsigned long long *total = totals + size_t(buf) * kDigitBins;
@@ -654,42 +703,81 @@ __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
 
 // The first kernel of a call that splits: the state reset (as prune_init_kernel,
 // except `fine`, which the previous call's count left at zero), then the sample:
-// the histogram of the keys' first SAMPLE_BITS bits over ranges of chunk elements
-// range_stride apart (one range per wave), added into `fine` (32-bit totals: only
+// the histogram of the keys' first SAMPLE_BITS bits over pieces of kPieceLanes vectors
+// piece_stride elements apart in W padded to whole vectors, added into `fine` (32-bit
+// totals: only
 // the bracket depends on them, and a bracket that misses the K-th key, as one from
 // a workspace that held something else would, costs passes over W, not exactness).
-template <typename Bits, bool ALIGNED>
+template <typename Bits>
 __global__ __launch_bounds__(kHistThreads) void prune_sample_kernel(
-    const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t chunk,
-    int64_t range_stride, uint32_t *__restrict__ fine, int64_t k, PruneState *slots,
+    const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t pieces,
+    int64_t piece_stride, uint32_t *__restrict__ fine, int64_t k, PruneState *slots,
     SplitInfo *info, int64_t *counts, int64_t *eq, int64_t *gt1, uint64_t *totals) {
-    constexpr int KB = PruneTraits<Bits>::KEY_BITS;
-    constexpr int FB = PruneTraits<Bits>::SAMPLE_BITS;
+    using Tr = PruneTraits<Bits>;
+    constexpr int KB = Tr::KEY_BITS;
+    constexpr int FB = Tr::SAMPLE_BITS;
+    constexpr int VEC = Tr::VEC;
     constexpr uint32_t shift = uint32_t(KB - FB);
     __shared__ uint32_t hist[1 << FB];
+    // the thread's vectors, on their way while the state is reset
+    const int64_t Np = padded_n<Bits>(N);
+    const double inv = 1.0 / double(Np);
+    const int64_t total = M * Np;
+    const int64_t threads = int64_t(gridDim.x) * kHistThreads;
+    const int64_t first = int64_t(blockIdx.x) * kHistThreads + threadIdx.x;
+    const int64_t vectors = pieces * kPieceLanes;
+    PVec<Bits, VEC> v[kSampleLoads];
+    int64_t left[kSampleLoads];                         // elements of the row from the vector on
+    auto load = [&](int64_t i0) {
+#pragma unroll
+        for (int u = 0; u < kSampleLoads; ++u) {
+            const int64_t i = i0 + u * threads;
+            const int64_t e = (i / kPieceLanes) * piece_stride + (i % kPieceLanes) * VEC;
+            const bool in = i < vectors && e < total;
+            const int64_t ec = in ? e : 0;
+            int64_t r = int64_t(double(ec) * inv);      // its row, or one off
+            r -= r * Np > ec ? 1 : 0;
+            r += (r + 1) * Np <= ec ? 1 : 0;
+            const int64_t c = ec - r * Np;              // < Np; c % VEC == 0
+            const Bits *at = W + r * ldw + c;
+            left[u] = in ? N - c : 0;
+            if (N - c >= VEC) {
+                typedef typename RowVec<Bits>::T RV;
+                const RV t = *reinterpret_cast<const RV *>(at);
+                v[u] = __builtin_bit_cast(PVec<Bits, VEC>, t);
+            } else {
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) v[u].e[j] = at[c + j < N ? j : 0];
+            }
+        }
+    };
+    load(first);
     for (int i = int(threadIdx.x); i < (1 << FB); i += kHistThreads) hist[i] = 0;
-    {
-        const int64_t stride = int64_t(gridDim.x) * kHistThreads;
-        const int64_t first = int64_t(blockIdx.x) * kHistThreads + threadIdx.x;
-        for (int64_t i = first; i < M; i += stride) {
-            counts[i] = 0;
-            eq[i] = 0;
-            gt1[i] = 0;
-        }
-        for (int64_t i = first; i < int64_t(kTotalsBuffers) * kDigitBins; i += stride)
-            totals[i] = 0;
-        if (first == 0) {
-            *info = SplitInfo{};
-            hand_on(slots, first_pass(KB, k), 0, 0);
-        }
+    for (int64_t i = first; i < M; i += threads) {
+        counts[i] = 0;
+        eq[i] = 0;
+        gt1[i] = 0;
+    }
+    for (int64_t i = first; i < int64_t(kTotalsBuffers) * kDigitBins; i += threads) totals[i] = 0;
+    if (first == 0) {
+        *info = SplitInfo{};
+        hand_on(slots, first_pass(KB, k), 0, 0);
     }
     __syncthreads();
-    for_each_key<Bits, ALIGNED>(W, ldw, M, N, chunk, range_stride, [](int64_t) {},
-                                [&](uint32_t key) { atomicAdd(&hist[key >> shift], 1u); });
+    for (int64_t i0 = first;; ) {
+#pragma unroll
+        for (int u = 0; u < kSampleLoads; ++u)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j)
+                if (j < left[u]) atomicAdd(&hist[(uint32_t(v[u].e[j]) & Tr::MAG) >> shift], 1u);
+        i0 += kSampleLoads * threads;
+        if (i0 >= vectors) break;
+        load(i0);
+    }
     __syncthreads();
     for (int b = int(threadIdx.x); b < (1 << FB); b += kHistThreads) {
-        const uint32_t v = hist[b];
-        if (v) atomicAdd(&fine[b], v);
+        const uint32_t n = hist[b];
+        if (n) atomicAdd(&fine[b], n);
     }
 }
 
@@ -743,7 +831,9 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
     uint64_t *mine = buf_lds + wave * kWaveRoom;
     uint32_t *hmine = hist + (int(threadIdx.x) & (kCopies - 1)) * kStride;
     uint32_t dlo = 0, dhi = 0;
+    uint32_t cbase = 0, cshift = 0, cwidth = 0;         // the candidates' first digit
     bool single = true;
+    for (int i = int(threadIdx.x); i < kCopies * kStride; i += kHistThreads) hist[i] = 0;
     // the bracket, the split info and the next state slot (and, without `single`,
     // the cleared histogram)
     auto hook = [&]() {
@@ -758,9 +848,11 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
             // nothing chosen yet
             hand_on(slots + (rd ^ 1), first_pass(KB, k), single ? 0 : CB, buf);
         }
-        if (!single) {
-            for (int i = int(threadIdx.x); i < kCopies * kStride; i += kHistThreads) hist[i] = 0;
-            __syncthreads();
+        if (single) {
+            cbase = dlo << first_shift;
+            const uint32_t bits = bracket_bits<Bits>(dlo, dhi);
+            cwidth = uint32_t(digit_width(int(bits)));
+            cshift = bits - cwidth;
         }
     };
     // the wave's candidates so far and its keys above the bracket (wave-uniform):
@@ -835,8 +927,10 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
                 const uint32_t p = wn + __builtin_amdgcn_mbcnt_hi(
                                              uint32_t(bal >> 32),
                                              __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
-                if (((cm >> j) & 1u) && p < uint32_t(kWaveRoom))
-                    mine[p] = (uint64_t(cur) << 32) | keys[j];
+                if ((cm >> j) & 1u) {
+                    if (p < uint32_t(kWaveRoom)) mine[p] = (uint64_t(cur) << 32) | keys[j];
+                    atomicAdd(&hmine[(keys[j] - cbase) >> cshift], 1u);
+                }
                 wn += uint32_t(__popcll(bal));
             }
         }
@@ -848,20 +942,23 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
                                         process(keys, mask);
                                     });
     } else {
-        for_each_round<Bits, false>(W, ldw, M, N, per_wave, per_wave, on_unit,
-                                    [&](const uint32_t (&keys)[K], uint32_t mask) {
-                                        process(keys, mask);
-                                    });
+        for_each_round<Bits>(W, ldw, M, N, per_wave, on_unit,
+                             [&](const uint32_t (&keys)[K], uint32_t mask) {
+                                 process(keys, mask);
+                             });
     }
-    if (!single) {                                      // uniform
-        __syncthreads();
+    auto flush_hist = [&](int bins) {
         unsigned long long *total = totals + size_t(buf) * kDigitBins;
-        for (int b = int(threadIdx.x); b < (1 << CB); b += kHistThreads) {
+        for (int b = int(threadIdx.x); b < bins; b += kHistThreads) {
             uint32_t v = 0;
 #pragma unroll
             for (int c = 0; c < kCopies; ++c) v += hist[c * kStride + b];
             if (v) atomicAdd(&total[b], (unsigned long long)v);
         }
+    };
+    if (!single) {                                      // uniform
+        __syncthreads();
+        flush_hist(1 << CB);
         return;
     }
     flush();
@@ -870,6 +967,7 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
         L.wave_tot[wave] = w_above;
     }
     __syncthreads();
+    flush_hist(1 << cwidth);                            // unused if some candidates do not fit
     if (threadIdx.x == 0) {
         uint32_t n = 0;
         bool over = false;
@@ -930,7 +1028,7 @@ __device__ __forceinline__ void take_ties(int64_t M, int64_t need,
 // once the pending digit is chosen.  From the candidates when they hold the
 // threshold (plus the split pass's gt1), else from W.  When only some keys == t
 // are kept, the last workgroup to finish then adds those.
-template <typename Bits, bool ALIGNED>
+template <typename Bits>
 __global__ __launch_bounds__(kHistThreads) void prune_count_kernel(
     const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t per_wave,
     const PruneState *__restrict__ slots, SplitInfo *__restrict__ info,
@@ -1012,8 +1110,8 @@ __global__ __launch_bounds__(kHistThreads) void prune_count_kernel(
         };
         // flush the previous row's counts when the wave moves on to a new row (all
         // lanes take part in the reduction)
-        for_each_key<Bits, ALIGNED>(
-            W, ldw, M, N, per_wave, per_wave,
+        for_each_key<Bits>(
+            W, ldw, M, N, per_wave,
             [&](int64_t r) {
                 if (r != cur) {
                     flush();
@@ -1148,8 +1246,9 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
     if (init_blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     // the state reset: its own launch, unless the sample (the first kernel of a call
     // that splits) does it
-    const bool split = k > 0 && M * N * int64_t(sizeof(Bits)) >= kSplitMinBytes;
-    if (!split)
+    const bool split = k > 0 && M * N >= kSplitMinElems;
+    const bool reset = !split || M * N * int64_t(sizeof(Bits)) < kResetInSample;
+    if (reset)
         hipLaunchKernelGGL(prune_init_kernel, dim3(unsigned(init_blocks)), dim3(256), 0, s, M,
                            k, int(Tr::KEY_BITS), w.slots, w.info, counts, w.eq, w.gt1, w.totals,
                            w.fine);
@@ -1168,37 +1267,27 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
         std::min<uint64_t>(cap / 2, uint64_t(groups) * uint64_t(kSplitLds) / 2);
     int rd = 0;                                         // the state slot the next kernel reads
     auto hist = [&](int buf, int role) {
-        if (aligned)
-            hipLaunchKernelGGL((prune_hist_kernel<Bits, true>), dim3(groups), dim3(kHistThreads),
-                               0, s, W, ldw, M, N, per_wave, w.slots, w.info, totals_u, w.cand,
-                               rd, buf, role, k, cap);
-        else
-            hipLaunchKernelGGL((prune_hist_kernel<Bits, false>), dim3(groups),
-                               dim3(kHistThreads), 0, s, W, ldw, M, N, per_wave, w.slots, w.info,
-                               totals_u, w.cand, rd, buf, role, k, cap);
+        hipLaunchKernelGGL((prune_hist_kernel<Bits>), dim3(groups), dim3(kHistThreads), 0, s, W,
+                           ldw, M, N, per_wave, w.slots, w.info, totals_u, w.cand, rd, buf, role,
+                           k, cap);
         rd ^= 1;
     };
     // the split pass pays for its extra launches only on large matrices: below
-    // kSplitMinBytes of W every pass streams W
+    // kSplitMinElems every pass streams W
     if (split) {
-        // the sample (ranges of kSampleChunk vectors per lane, one out of about every
-        // kSampleEvery, the stride drifting by an odd number of vectors so that it
-        // does not follow power-of-two rows), in as many workgroups as it has ranges
-        // for; the split pass then reads W once
-        const int64_t chunk = kSampleChunk * int64_t(kWave) * Tr::VEC;
-        const int64_t range_stride = kSampleEvery * chunk + kSampleDrift * Tr::VEC;
-        const int64_t ranges = (M * padded_n<Bits>(N) + range_stride - 1) / range_stride;
+        // the sample (one piece out of about kSampleEvery, the stride drifting by an odd
+        // number of vectors so that it does not follow power-of-two rows), in as many
+        // workgroups as it has loads for; the split pass then reads W once
+        const int64_t piece = kPieceLanes * Tr::VEC;
+        const int64_t piece_stride = kSampleEvery * piece + kSampleDrift * Tr::VEC;
+        const int64_t pieces = (M * padded_n<Bits>(N) + piece_stride - 1) / piece_stride;
+        const int64_t per_group = int64_t(kHistThreads) * kSampleLoads;
         const int64_t sample_groups =
-            std::min<int64_t>(kSampleGroups, (ranges + kHistWaves - 1) / kHistWaves);
-        const dim3 sgrid(unsigned(std::max<int64_t>(1, sample_groups)));
-        if (aligned)
-            hipLaunchKernelGGL((prune_sample_kernel<Bits, true>), sgrid, dim3(kHistThreads), 0, s,
-                               W, ldw, M, N, chunk, range_stride, w.fine, k, w.slots, w.info,
-                               counts, w.eq, w.gt1, w.totals);
-        else
-            hipLaunchKernelGGL((prune_sample_kernel<Bits, false>), sgrid, dim3(kHistThreads), 0,
-                               s, W, ldw, M, N, chunk, range_stride, w.fine, k, w.slots, w.info,
-                               counts, w.eq, w.gt1, w.totals);
+            std::min<int64_t>(kSampleGroups, (pieces * kPieceLanes + per_group - 1) / per_group);
+        hipLaunchKernelGGL((prune_sample_kernel<Bits>),
+                           dim3(unsigned(std::max<int64_t>(1, sample_groups))),
+                           dim3(kHistThreads), 0, s, W, ldw, M, N, pieces, piece_stride, w.fine, k,
+                           w.slots, w.info, counts, w.eq, w.gt1, w.totals);
         if (aligned)
             hipLaunchKernelGGL((prune_split_kernel<Bits, true>), dim3(groups), dim3(kHistThreads),
                                0, s, W, ldw, M, N, per_wave, w.slots, w.info, totals_u, w.fine,
@@ -1215,14 +1304,9 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
     }
     auto *gt_u = reinterpret_cast<unsigned long long *>(counts);
     auto *eq_u = reinterpret_cast<unsigned long long *>(w.eq);
-    if (aligned)
-        hipLaunchKernelGGL((prune_count_kernel<Bits, true>), dim3(groups), dim3(kHistThreads), 0,
-                           s, W, ldw, M, N, per_wave, w.slots, w.info, totals_u, gt_u, eq_u,
-                           w.cand, gt1_u, cap, rd, w.fine);
-    else
-        hipLaunchKernelGGL((prune_count_kernel<Bits, false>), dim3(groups), dim3(kHistThreads), 0,
-                           s, W, ldw, M, N, per_wave, w.slots, w.info, totals_u, gt_u, eq_u,
-                           w.cand, gt1_u, cap, rd, w.fine);
+    hipLaunchKernelGGL((prune_count_kernel<Bits>), dim3(groups), dim3(kHistThreads), 0, s, W, ldw,
+                       M, N, per_wave, w.slots, w.info, totals_u, gt_u, eq_u, w.cand, gt1_u, cap,
+                       rd, w.fine);
     return hipGetLastError();
 }
 
