@@ -1,7 +1,9 @@
 // Host side of the DARB library: plan construction (section 3.2 block-size
 // rule and grouped layout), argument checking and dispatch to the kernels.
+#include <chrono>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -276,6 +278,77 @@ int darb_plan_upload(darb_plan *p, void *workspace, int64_t workspace_bytes, voi
 
 void darb_plan_destroy(darb_plan *p) { delete p; }
 
+}  // extern "C"
+
+namespace {
+
+// Pinned memory through which plan launches hand their summary to the host: one small
+// allocation for the process, a slot of it per call in progress.  A call that finds no
+// slot free copies the summary instead.
+class SummarySlots {
+public:
+    PlanSummary *take() {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!base_ && !failed_) {
+            void *m = nullptr;
+            if (hipHostMalloc(&m, kSlots * sizeof(Slot), hipHostMallocPortable) != hipSuccess) {
+                (void)hipGetLastError();
+                failed_ = true;
+                return nullptr;
+            }
+            base_ = static_cast<Slot *>(m);
+            for (int i = 0; i < kSlots; ++i) free_[n_free_++] = base_ + i;
+        }
+        if (n_free_ == 0) return nullptr;
+        PlanSummary *p = &free_[--n_free_]->s;
+        __atomic_store_n(&p->ready, 0u, __ATOMIC_RELAXED);
+        return p;
+    }
+    void give_back(PlanSummary *p) {
+        std::lock_guard<std::mutex> lock(mu_);
+        free_[n_free_++] = reinterpret_cast<Slot *>(p);
+    }
+
+private:
+    static constexpr int kSlots = 16;
+    struct alignas(512) Slot {
+        PlanSummary s;
+    };
+    std::mutex mu_;
+    Slot *base_ = nullptr;
+    Slot *free_[kSlots] = {};
+    int n_free_ = 0;
+    bool failed_ = false;
+};
+
+SummarySlots summary_slots;
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Until the launch has set its flag.  The host looks at it for a while (what is queued
+// before it is rarely longer), then waits for the stream, which also reports errors.
+hipError_t wait_ready(const PlanSummary *p, hipStream_t s) {
+    const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    for (int i = 1;; ++i) {
+        if (__atomic_load_n(&p->ready, __ATOMIC_ACQUIRE)) return hipSuccess;
+        if ((i & 63) == 0 && std::chrono::steady_clock::now() >= end) break;
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    return __atomic_load_n(&p->ready, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
+}
+
+}  // namespace
+
+extern "C" {
+
 static int64_t device_plan_bytes(int64_t M) {
     return perm_bytes(M) + (M * int64_t(sizeof(int64_t)) + 255) / 256 * 256 +
            plan_device_scratch_bytes(M);
@@ -320,12 +393,23 @@ int darb_plan_create_device(int64_t M, int64_t N, const int64_t *row_count, int6
     int64_t *d_rowinfo = reinterpret_cast<int64_t *>(base + perm_bytes(M));
     void *scratch = base + perm_bytes(M) + (M * int64_t(sizeof(int64_t)) + 255) / 256 * 256;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    e = launch_plan_device(M, N, row_count, kept, round_mode, log2_exact(b_min), log2_exact(b_max),
-                           d_perm, d_rowinfo, scratch, s);
     int64_t summary[4 * kMaxBins];
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(summary, scratch, sizeof(summary), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const int lmin = log2_exact(b_min), lmax = log2_exact(b_max);
+    PlanSummary *slot = plan_one_launch(M) && !capturing(s) ? summary_slots.take() : nullptr;
+    if (slot) {
+        e = launch_plan_one(M, N, row_count, kept, round_mode, lmin, lmax, d_perm, d_rowinfo, slot, s);
+        if (e == hipSuccess) e = wait_ready(slot, s);
+        if (e == hipSuccess) {
+            std::memcpy(summary, slot->v, sizeof(summary));
+            summary_slots.give_back(slot);
+        }                                       // else the launch may still write to the slot
+    } else {
+        e = launch_plan_device(M, N, row_count, kept, round_mode, lmin, lmax, d_perm, d_rowinfo,
+                               scratch, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(summary, scratch, sizeof(summary), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
     if (e != hipSuccess) return fail(DARB_E_HIP, std::string("device plan: ") + hipGetErrorString(e));
     darb_plan *p = new (std::nothrow) darb_plan();
     if (!p) return fail(DARB_E_NOMEM, "plan allocation");

@@ -124,6 +124,16 @@ hipError_t launch_lstm_cell(int64_t H, int64_t batch, const float *G, const floa
 // group summary (rows, first_row, first_elem, first_word: 8 int64 each) at the start
 // of `scratch` (plan_device_scratch_bytes(M), 256-byte aligned).
 int64_t plan_device_scratch_bytes(int64_t M);
+// The same in one launch for few rows (plan_one_launch): the summary goes to pinned host
+// memory and `ready` is set (system scope) once it and the tables are complete.
+struct PlanSummary {
+    int64_t v[4 * kMaxBins];
+    uint32_t ready;
+};
+bool plan_one_launch(int64_t M);
+hipError_t launch_plan_one(int64_t M, int64_t N, const int64_t *counts, int64_t kept, int mode,
+                           int lmin, int lmax, int32_t *perm, int64_t *rowinfo, PlanSummary *host,
+                           hipStream_t s);
 hipError_t launch_plan_device(int64_t M, int64_t N, const int64_t *counts, int64_t kept, int mode,
                               int lmin, int lmax, int32_t *perm, int64_t *rowinfo, void *scratch,
                               hipStream_t s);

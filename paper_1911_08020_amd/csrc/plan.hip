@@ -12,7 +12,15 @@
 // host compares fp64 quotients, and two distinct quotients of this size never round
 // to the same double.
 //
-// Three launches: per-row block size and per-workgroup group counts; one workgroup scans
+// Up to kPlanOneRows rows, one launch of one workgroup, which holds every row's block
+// size in registers; it hands the group summary to the host itself, through pinned memory
+// and a flag, so that the host neither copies nor waits for the stream.  The rows of such
+// a plan are few enough that three launches, a copy and the wait for it cost several times
+// the work: 4096 rows, 5.0 + 2.6 + 3.4 us of kernels and 2.3 us of copy before, 8.3 us
+// now, and a compression of 4096 x 9216 fp32 (pruning, plan, encode, packing, codes) 158
+// -> 112 us, part of it from the pruning.  (Every thread fencing for itself: 12.4 us.)
+//
+// Otherwise three launches: per-row block size and per-workgroup group counts; one workgroup scans
 // those counts into group starts and each workgroup's first position per group (and
 // writes the group summary the host reads back); each row then takes its place --
 // workgroup start plus its rank among the workgroup's rows of the same group, counted
@@ -25,13 +33,15 @@ namespace {
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kGroups = kMaxBins;               // log2 b = 0 .. 7
+constexpr int64_t kPlanOneRows = 16 * kPlanThreads;
 
 __device__ __forceinline__ int row_log2b_counts(int64_t c, int64_t N, int64_t M, int64_t kept,
                                                 int mode, int lmin, int lmax) {
     if (c <= 0) return lmax;
     if (c > N) c = N;
-    int l = 0;                                  // largest l with (c << l) <= N
-    while (l < 62 && (c << (l + 1)) <= N) ++l;
+    int l = 0;                                  // largest l with (c << l) <= N, or past lmax
+#pragma unroll
+    for (int i = 1; i <= kMaxLog2B + 1; ++i) l += (c << i) <= N ? 1 : 0;
     const bool exact = (c << l) == N;
     const bool up = (mode == DARB_ROUND_FLOOR) || (c * M >= kept);
     if (!up && !exact) ++l;
@@ -126,6 +136,95 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scan_kernel(
     }
 }
 
+// Everything above and below in one workgroup: rows t * 1024 + thread, TILES of them per
+// thread.  `host` (pinned): the summary, then the flag.  The tables are written back
+// before the flag goes out: whoever the host tells about it finds them complete.
+template <int TILES>
+__global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
+    int64_t M, int64_t N, const int64_t *__restrict__ counts, int64_t kept, int mode, int lmin,
+    int lmax, int64_t *__restrict__ rowinfo, int32_t *__restrict__ perm, PlanSummary *host) {
+    constexpr int kParts = TILES * kPlanWaves;           // (tile, wave) pairs, in row order
+    constexpr int kPer = (kParts + kWave - 1) / kWave;   // of them per lane of the scan
+    __shared__ int part[kGroups][kParts];                // rows of each pair, then the rows before
+    __shared__ int64_t total[kGroups], first_row[kGroups], first_elem[kGroups];
+    const int lane = int(threadIdx.x) & (kWave - 1);
+    const int wave = int(threadIdx.x) / kWave;
+    int64_t c[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {                    // all loads first
+        const int64_t r = int64_t(t) * kPlanThreads + threadIdx.x;
+        c[t] = counts[r < M ? r : M - 1];
+    }
+    int l[TILES], rank[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        const int64_t r = int64_t(t) * kPlanThreads + threadIdx.x;
+        l[t] = row_log2b_counts(c[t], N, M, kept, mode, lmin, lmax);
+        int cnt[kGroups];
+        rank[t] = wave_rank(l[t], r < M, cnt);
+        if (lane == 0) {
+#pragma unroll
+            for (int v = 0; v < kGroups; ++v) part[v][t * kPlanWaves + wave] = cnt[v];
+        }
+    }
+    __syncthreads();
+    if (wave < kGroups) {                                // one wave per group
+        int own[kPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int at = lane * kPer + i;
+            own[i] = at < kParts ? part[wave][at] : 0;
+            sum += own[i];
+        }
+        int incl = sum;
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) {
+            const int o = __shfl_up(incl, m, kWave);
+            if (lane >= m) incl += o;
+        }
+        int before = incl - sum;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int at = lane * kPer + i;
+            if (at < kParts) part[wave][at] = before;
+            before += own[i];
+        }
+        if (lane == kWave - 1) total[wave] = incl;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t row = 0, elem = 0, word = 0;
+        for (int g = 0; g < kGroups; ++g) {
+            const int64_t nblk = (N + (int64_t(1) << g) - 1) >> g;
+            first_row[g] = row;
+            first_elem[g] = elem;
+            host->v[g] = total[g];
+            host->v[kGroups + g] = row;
+            host->v[2 * kGroups + g] = elem;
+            host->v[3 * kGroups + g] = word;
+            row += total[g];
+            elem += total[g] * nblk;
+            word += (total[g] * nblk + 31) / 32 * g;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        const int64_t r = int64_t(t) * kPlanThreads + threadIdx.x;
+        if (r < M) {
+            const int in_group = part[l[t]][t * kPlanWaves + wave] + rank[t];
+            const int64_t nblk = (N + (int64_t(1) << l[t]) - 1) >> l[t];
+            perm[first_row[l[t]] + in_group] = int32_t(r);
+            rowinfo[r] = ((first_elem[l[t]] + in_group * nblk) << 8) | l[t];
+        }
+    }
+    // every wave's table stores are in this XCD's L2 when the barrier lets go; the release
+    // then writes that back and sets the flag
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&host->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Each row's storage position: its workgroup's first position in its group plus its
 // rank among the workgroup's earlier rows of that group.
 __global__ __launch_bounds__(kPlanThreads) void plan_place_kernel(
@@ -157,6 +256,20 @@ __global__ __launch_bounds__(kPlanThreads) void plan_place_kernel(
 int64_t plan_device_scratch_bytes(int64_t M) {
     const int64_t nwg = (M + kPlanThreads - 1) / kPlanThreads;
     return 4 * kGroups * int64_t(sizeof(int64_t)) + nwg * kGroups * int64_t(sizeof(int32_t));
+}
+
+bool plan_one_launch(int64_t M) { return M <= kPlanOneRows; }
+
+hipError_t launch_plan_one(int64_t M, int64_t N, const int64_t *counts, int64_t kept, int mode,
+                           int lmin, int lmax, int32_t *perm, int64_t *rowinfo, PlanSummary *host,
+                           hipStream_t s) {
+#define DARB_PLAN_ONE(T)                                                                      \
+    hipLaunchKernelGGL((plan_one_kernel<T>), dim3(1), dim3(kPlanThreads), 0, s, M, N, counts,  \
+                       kept, mode, lmin, lmax, rowinfo, perm, host)
+    if (M <= 4 * kPlanThreads) DARB_PLAN_ONE(4);
+    else DARB_PLAN_ONE(16);
+#undef DARB_PLAN_ONE
+    return hipGetLastError();
 }
 
 hipError_t launch_plan_device(int64_t M, int64_t N, const int64_t *counts, int64_t kept, int mode,
