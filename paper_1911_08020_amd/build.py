@@ -9,8 +9,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdarb.so")
 CALL_MODULE = os.path.join(HERE, "_darbcall.so")
-SOURCES = ["api.cpp", "encode.hip", "product.hip", "product_i8.hip",
-           "lstm_seq.hip", "packed.hip", "prune.hip", "plan.hip", "misc.hip"]
+SOURCES = ["api.cpp", "encode.hip", "product.hip", "product_i8.hip", "lstm_seq.hip",
+           "packed.hip", "prune.hip", "plan.hip", "misc.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
