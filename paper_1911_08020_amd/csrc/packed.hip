@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint32_t *__rest
     }
     const PackedGroup pg = packed_group(packed, pick(bins.first_word, g), l);
     const int64_t j = i - pick(bins.first_elem, g);
-    offsets[i] = uint8_t(packed_bits32(packed_load2(pg, j)) & pg.mask);
+    offsets[i] = uint8_t(packed_bits32(packed_load4(pg, j)) & pg.mask);
 }
 
 }  // namespace

@@ -127,7 +127,8 @@ __device__ __forceinline__ int block_begin_of(const ProductSchedule &s, int g) {
 // Offset sources.  A lane loads the indices of NV consecutive retained weights of a
 // group (group slots j .. j + NV - 1, j a multiple of NV) as `Raw`, keeps them in
 // registers while other loads are in flight, turns them into `Bits` when it needs
-// them and reads index q with field().
+// them and reads index q with field().  row() and load_row() are the same for vector i of
+// a row that starts at a multiple of NV, with the row's part of the address formed once.
 // ---------------------------------------------------------------------------------
 
 struct GroupOffsets {
@@ -160,6 +161,11 @@ template <int NV> struct Off<false, NV> {
     __device__ static Raw load(const GroupOffsets &go, int64_t j) {
         return *reinterpret_cast<const Raw *>(go.u8 + j);
     }
+    struct Row { const uint8_t *at; };
+    __device__ static Row row(const GroupOffsets &go, int64_t j0) { return Row{go.u8 + j0}; }
+    __device__ static Raw load_row(const GroupOffsets &, const Row &r, int i) {
+        return *reinterpret_cast<const Raw *>(r.at + i * NV);
+    }
     __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return r; }
     __device__ static int field(const Bits &b, int q, const GroupOffsets &) {
         if constexpr (NV <= 4) return int((uint32_t(b) >> (8 * q)) & 0xFFu);
@@ -171,12 +177,17 @@ template <int NV> struct Off<false, NV> {
     }
 };
 
-// packed, up to 4 indices (<= 28 bits): two words
+// packed, up to 4 indices (<= 28 bits): 4 bytes
 template <int NV> struct Off<true, NV> {
     static_assert(NV <= 4, "wider vectors have their own specialisations");
-    using Raw = PackedWords2;
+    using Raw = Packed4;
     using Bits = uint32_t;
-    __device__ static Raw load(const GroupOffsets &go, int64_t j) { return packed_load2(go.pk, j); }
+    __device__ static Raw load(const GroupOffsets &go, int64_t j) { return packed_load4(go.pk, j); }
+    struct Row { int64_t j0; };
+    __device__ static Row row(const GroupOffsets &, int64_t j0) { return Row{j0}; }
+    __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
+        return load(go, r.j0 + int64_t(i) * NV);
+    }
     __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return packed_bits32(r); }
     __device__ static int field(Bits b, int q, const GroupOffsets &go) {
         return packed_field(b, q, go.pk);
@@ -186,11 +197,20 @@ template <int NV> struct Off<true, NV> {
     }
 };
 
-// packed, 8 indices (<= 56 bits): three words
+// packed, 8 indices (<= 56 bits): twice 4 bytes
 template <> struct Off<true, 8> {
-    using Raw = PackedWords3;
+    using Raw = Packed8;
     using Bits = uint64_t;
-    __device__ static Raw load(const GroupOffsets &go, int64_t j) { return packed_load3(go.pk, j); }
+    __device__ static Raw load(const GroupOffsets &go, int64_t j) {
+        return packed_load8(go.pk, packed_octet(go.pk, j >> 3), int(j >> 3), 0);
+    }
+    struct Row { const char *at; int v; };
+    __device__ static Row row(const GroupOffsets &go, int64_t j0) {
+        return Row{packed_octet(go.pk, j0 >> 3), int(j0 >> 3)};
+    }
+    __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
+        return packed_load8(go.pk, r.at, r.v, i);
+    }
     __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return packed_bits64(r); }
     __device__ static int field(Bits b, int q, const GroupOffsets &go) {
         return packed_field(b, q, go.pk);
@@ -203,10 +223,12 @@ template <> struct Off<true, 8> {
 // packed, 16 indices: two 8-index windows (j is a multiple of 16, so both lie in
 // one run)
 template <> struct Off<true, 16> {
-    struct Raw { PackedWords3 lo, hi; };
+    struct Raw { Packed8 lo, hi; };
     struct Bits { uint64_t lo, hi; };
     __device__ static Raw load(const GroupOffsets &go, int64_t j) {
-        return Raw{packed_load3(go.pk, j), packed_load3(go.pk, j + 8)};
+        const char *at = packed_octet(go.pk, j >> 3);
+        return Raw{packed_load8(go.pk, at, int(j >> 3), 0),
+                   packed_load8(go.pk, at, int(j >> 3), 1)};
     }
     __device__ static Bits bits(const Raw &r, const GroupOffsets &) {
         return Bits{packed_bits64(r.lo), packed_bits64(r.hi)};
@@ -634,6 +656,7 @@ __global__ __launch_bounds__(kSpmvThreads, 4) void spmv_rows_kernel(SpmvRowsArgs
         const int64_t j0 = int64_t(rc) * (int64_t(nvec) * VEC);   // the row's first slot in its group
         const typename WV::V *vrow =
             reinterpret_cast<const typename WV::V *>(values + first_elem + j0);
+        const typename OV::Row orow = OV::row(go, j0);
 #pragma unroll
         for (int k = 0; k < KV; ++k) {
             if (kAll || k < n) {                             // uniform
@@ -643,7 +666,7 @@ __global__ __launch_bounds__(kSpmvThreads, 4) void spmv_rows_kernel(SpmvRowsArgs
                 int vi = sub + k * L;
                 vi = vi < nvec ? vi : nvec - 1;
                 wv[k] = __builtin_nontemporal_load(vrow + vi);
-                ov[k] = OV::load(go, j0 + int64_t(vi) * VEC);
+                ov[k] = OV::load_row(go, orow, vi);
             }
         }
     };
