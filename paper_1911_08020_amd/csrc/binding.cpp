@@ -1,7 +1,7 @@
 // The per-token calls of the Python package, marshalled in native code: the products, the
 // encode and the conversions take 3 to 7 us on the GPU, and checking the tensors, fetching
-// the current stream and the foreign-function call took 9.7 us of Python per call (4.2 us now, of which the launch is
-// about 3).
+// the current stream and the foreign-function call took 9.7 us of Python per call (4.2 us
+// now, of which the launch is about 3).
 //
 // Each function does its method's own checks on plain tensors and makes the call.  For
 // whatever it does not take as it is (a tensor subclass, a wrong type, shape or device, a
