@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
     const int64_t *__restrict__ rowinfo, int64_t H, int64_t batch,
     const float *__restrict__ h_in, const float *__restrict__ U, int64_t ldu,
     float *__restrict__ c, float *__restrict__ h_out, float *__restrict__ h_seq,
-    int64_t ld_seq) {
+    int64_t ld_seq, int64_t nnz) {
     using XL = XLoad<float, CPL>;
     constexpr int L = 1 << LGL;
     constexpr int GM = L >= 16 ? 1 : 16 / L;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
             float v[GM];
             int o[GM];
             using PL = PairLoad<Tw, GM, false, true>;
-            PL::decode(PL::issue(values + r0, go, r0, ok ? k : k0, nblk), go, v, o);
+            PL::decode(PL::issue(values + r0, go, r0, ok ? k : k0, nnz - r0), go, v, o);
 #pragma unroll
             for (int gi = 0; gi < GM; ++gi) {
                 const bool okg = ok && k + gi < nblk;
@@ -145,7 +145,8 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
 int lstm_step_lgl(const darb_plan &whh, int64_t batch, int cpl) {
     const int64_t lanes = (batch + cpl - 1) / cpl;
     if (lanes > 16) return -1;
-    const int lgl = ilog2_ceil(lanes);
+    int lgl = ilog2_ceil(lanes);
+    if (whh.nnz < 16) lgl = 4;                          // no room for vectors of weights
     const int64_t S = 16;                               // L * GM for every L <= 16
     int64_t worst = 0;
     for (int g = 0; g < whh.bins.nbins; ++g) {
@@ -164,7 +165,7 @@ hipError_t launch_lstm_step_t(const darb_plan &whh, int lgl, const void *values,
 #define DARB_STEP(LGL)                                                                          \
     hipLaunchKernelGGL((lstm_step_kernel<Tw, CPL, LGL>), dim3(unsigned(H)), dim3(kStepThreads), \
                        0, st, v, offsets, whh.d_rowinfo, H, batch, h_in, U, ldu, c, h_out,       \
-                       h_seq, ld_seq)
+                       h_seq, ld_seq, whh.nnz)
     switch (lgl) {
         case 0: DARB_STEP(0); break;
         case 1: DARB_STEP(1); break;
