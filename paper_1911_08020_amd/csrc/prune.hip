@@ -967,7 +967,6 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
         L.wave_tot[wave] = w_above;
     }
     __syncthreads();
-    flush_hist(1 << cwidth);                            // unused if some candidates do not fit
     if (threadIdx.x == 0) {
         uint32_t n = 0;
         bool over = false;
@@ -991,6 +990,8 @@ __global__ __launch_bounds__(kHistThreads) void prune_split_kernel(
         if (above) atomicAdd(&info->n_above, (unsigned long long)above);
         base = b;
     }
+    // while the reservation is under way (unused if some candidates do not fit)
+    flush_hist(1 << cwidth);
     __syncthreads();
     if (base < cap) {                                   // uniform: the room was reserved
         uint64_t at = base;
