@@ -281,7 +281,7 @@ class Plan:
         h = getattr(self, "_h", None)
         if h is not None and h.value:
             _destroy(h)
-            self._h = None
+            self._h = self._ref = None
 
     @property
     def handle(self):
