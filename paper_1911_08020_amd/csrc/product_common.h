@@ -128,7 +128,8 @@ __device__ __forceinline__ int block_begin_of(const ProductSchedule &s, int g) {
 // group (group slots j .. j + NV - 1, j a multiple of NV) as `Raw`, keeps them in
 // registers while other loads are in flight, turns them into `Bits` when it needs
 // them and reads index q with field().  row() and load_row() are the same for vector i of
-// a row that starts at a multiple of NV, with the row's part of the address formed once.
+// a row that starts at a multiple of NV; for 8 packed indices the row's part of the
+// address is formed once.
 // ---------------------------------------------------------------------------------
 
 struct GroupOffsets {
@@ -161,10 +162,10 @@ template <int NV> struct Off<false, NV> {
     __device__ static Raw load(const GroupOffsets &go, int64_t j) {
         return *reinterpret_cast<const Raw *>(go.u8 + j);
     }
-    struct Row { const uint8_t *at; };
-    __device__ static Row row(const GroupOffsets &go, int64_t j0) { return Row{go.u8 + j0}; }
-    __device__ static Raw load_row(const GroupOffsets &, const Row &r, int i) {
-        return *reinterpret_cast<const Raw *>(r.at + i * NV);
+    struct Row { int64_t j0; };
+    __device__ static Row row(const GroupOffsets &, int64_t j0) { return Row{j0}; }
+    __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
+        return load(go, r.j0 + int64_t(i) * NV);
     }
     __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return r; }
     __device__ static int field(const Bits &b, int q, const GroupOffsets &) {
