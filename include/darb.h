@@ -323,9 +323,11 @@ int darb_prune_counts_noalloc(int64_t M, int64_t N, int wdtype, const void *W, i
  * W_ih is [4H x I] and W_hh is [4H x H], both of wdtype, each with its own
  * uploaded plan.  The input products of all steps are computed first as one
  * darb_spmm with B = T * batch.  The time steps then run as one launch whose
- * workgroups keep W_hh and exchange h through the workspace (T >= 16, batch <= 64, W_hh
- * rows of at most 512 retained weights, H up to about 4000 at batch <= 32, not under
- * stream capture).  Such launches follow each other on a device whatever their streams;
+ * workgroups keep W_hh and exchange h through the workspace.  That takes T >= 16, W_hh
+ * rows of at most 512 retained weights, no stream capture, H of 16 to 4095 at batch <= 16,
+ * 2048 at batch <= 32, 1024 at batch <= 64, and W_hh's weights in the workgroups'
+ * registers: the ceil(H / 32) units of each (of 32) hold at most 1536 chunks of 16 weights
+ * (1024 at batch > 32), each gate row in whole chunks.  Such launches follow each other on a device whatever their streams;
  * a workgroup's waits are bounded, and a sequence whose workgroups could not all run at
  * once (another process holding the device) is computed again without waiting, with the
  * same result bit for bit.  Otherwise each time step is one launch: a workgroup per

@@ -1,5 +1,6 @@
 // Host side of the DARB library: plan construction (section 3.2 block-size
 // rule and grouped layout), argument checking and dispatch to the kernels.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -180,6 +181,12 @@ int darb_plan_create(int64_t M, int64_t N, const double *row_density, double mat
         p->perm[i] = int32_t(r);
         p->row_start[r] = group_elem[l];
         group_elem[l] += nblk;
+    }
+    if (lstm_shape(M, N)) {
+        int64_t held[kLstmMembers] = {0};
+        for (int64_t r = 0; r < M; ++r)
+            held[r % N / lstm_units(N)] += lstm_row_chunks(N, p->log2b[r]);
+        p->lstm_chunks = *std::max_element(held, held + kLstmMembers);
     }
     p->workspace_bytes = perm_bytes(M) + M * int64_t(sizeof(int64_t));
     *out = p;
@@ -431,7 +438,7 @@ int darb_plan_create_device(int64_t M, int64_t N, const int64_t *row_count, int6
             bt.rows[g] = rows;
             bt.first_elem[g] = summary[2 * kMaxBins + l];
             bt.nblk[g] = nblk;
-            bt.first_word[g] = summary[3 * kMaxBins + l];
+            bt.first_word[g] = words;
         }
         elem += rows * nblk;
         words += (rows * nblk + 31) / 32 * l;
@@ -442,6 +449,7 @@ int darb_plan_create_device(int64_t M, int64_t N, const int64_t *row_count, int6
     }
     p->nnz = elem;
     p->packed_words = words;
+    p->lstm_chunks = summary[kSummaryLstm];
     p->workspace_bytes = need;
     p->d_perm = d_perm;
     p->d_rowinfo = d_rowinfo;

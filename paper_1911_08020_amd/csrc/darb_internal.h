@@ -39,6 +39,25 @@ struct ProductSchedule {
     int32_t stage_loads;              // SpMV: 16-byte loads per thread to stage x
 };
 
+// The LSTM sequence launch gives the H hidden units of a [4H x H] matrix evenly to at most
+// kLstmMembers workgroups, lstm_units(H) each, and cuts every gate row of a unit into
+// chunks of kLstmChunk retained weights.
+constexpr int kLstmMembers = 32;
+constexpr int kLstmChunk = 16;
+constexpr int64_t kLstmMaxHidden = 4096;
+__host__ __device__ constexpr int64_t lstm_units(int64_t H) {
+    return (H + kLstmMembers - 1) / kLstmMembers;
+}
+// Whether an M x N matrix can be its recurrent one.
+__host__ __device__ constexpr bool lstm_shape(int64_t M, int64_t N) {
+    return N <= kLstmMaxHidden && M == 4 * N;
+}
+// Chunks of one row with block size 2^l.
+__host__ __device__ constexpr int64_t lstm_row_chunks(int64_t N, int l) {
+    return ((N + (int64_t(1) << l) - 1) >> l) / kLstmChunk +
+           (((N + (int64_t(1) << l) - 1) >> l) % kLstmChunk != 0 ? 1 : 0);
+}
+
 }  // namespace darb
 
 struct darb_plan {
@@ -50,6 +69,7 @@ struct darb_plan {
     darb::BinTable bins{};
     int64_t workspace_bytes = 0;
     int64_t packed_words = 0;       // 32-bit words of the bit-packed offsets
+    int64_t lstm_chunks = 0;        // lstm_shape: the most chunks of one LSTM workgroup
     // device side (inside the caller's workspace)
     int32_t *d_perm = nullptr;      // [M] original row stored i-th
     int64_t *d_rowinfo = nullptr;   // [M] (row_start[r] << 8) | log2b[r], original order
@@ -122,7 +142,9 @@ hipError_t launch_lstm_cell(int64_t H, int64_t batch, const float *G, const floa
                             hipStream_t s);
 // The plan's storage order and per-row table from device-side kept counts, and the
 // group summary (rows, first_row, first_elem, first_word: 8 int64 each) at the start
-// of `scratch` (plan_device_scratch_bytes(M), 256-byte aligned).
+// of `scratch` (plan_device_scratch_bytes(M), 256-byte aligned).  The first group's first
+// word is 0, so its place carries the plan's lstm_chunks.
+constexpr int kSummaryLstm = 3 * kMaxBins;
 int64_t plan_device_scratch_bytes(int64_t M);
 // The same in one launch for few rows (plan_one_launch): the summary goes to pinned host
 // memory and `ready` is set (system scope) once it and the tables are complete.
@@ -143,3 +165,9 @@ hipError_t launch_stream_read_shape(const void *buf, int64_t bytes, int threads,
 hipError_t launch_stream_copy(void *dst, const void *src, int64_t bytes, hipStream_t s);
 
 }  // namespace darb
+
+// What the tests look at from outside (no part of the ABI): a plan's lstm_chunks, and
+// whether the LSTM layer's time steps would run as one launch.
+extern "C" int64_t darb_test_lstm_chunks(const darb_plan *whh);
+extern "C" int darb_test_lstm_seq_applies(const darb_plan *whh, int64_t H, int64_t T,
+                                          int64_t batch, void *stream);

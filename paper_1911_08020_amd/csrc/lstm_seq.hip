@@ -46,9 +46,9 @@ namespace {
 
 constexpr int kSeqThreads = 512;
 constexpr int kSeqXcds = 8;           // workgroups are handed to the XCDs in turn
-constexpr int kSeqMembers = 32;       // most workgroups per group: an XCD's CUs
-constexpr int kSeqChunk = 16;         // weights per chunk: one thread's unit of work
-// chunks per thread kept in registers (the LDS holds one sum of each)
+constexpr int kSeqMembers = kLstmMembers;   // most workgroups per group: an XCD's CUs
+constexpr int kSeqChunk = kLstmChunk;       // weights per chunk: one thread's unit of work
+// chunks per thread, kept in registers (the LDS holds one sum of each)
 constexpr int seq_resident(int cpg) { return cpg == 8 ? 2 : 3; }
 constexpr int kSeqMaxRows = kSeqThreads;   // gate rows of a member: one thread each
 constexpr int kSeqMaxNblk = 512;      // retained weights per row (at most 64 chunks)
@@ -338,9 +338,13 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
         else
             __hip_atomic_store(base + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    // Every step, with the sums of the chunks from gather(base, n): base .. base + n - 1.
-    // False if some member gave up.
-    auto steps = [&](auto &&gather) -> bool {
+    // the member's chunks, in registers for the whole sequence (the launch's rule: they fit)
+    Chunk<Tw> res[kRes];
+#pragma unroll
+    for (int j = 0; j < kRes; ++j) {
+        const int id = tid + j * kSeqThreads;
+        fetch(res[j], id < chunks ? id : chunks - 1);
+    }
     for (int t = 0; t < A.T; ++t) {
 #pragma unroll
         for (int s = 0; s < kItems; ++s) ug[s] = ug_next[s];
@@ -391,7 +395,11 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
             }
         }
         __syncthreads();
-        if (*bad) return false;                              // uniform: same value for all
+        if (*bad) {                                          // uniform: same value for all
+            if (tid == 0)
+                __hip_atomic_store(A.failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
         // every member has finished with h_{t-2} (at step 1: with the XCD numbers): its
         // slot takes h_{t+1} next
         if (t >= 1) {
@@ -400,41 +408,38 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
                 if ((it & 3) == 0)
                     publish(old, uint32_t(u0 * CPG + (it >> 2)), kSentinel);
         }
+#pragma unroll
+        for (int j = 0; j < kRes; ++j) {
+            const int id = j * kSeqThreads + tid;
+            if (j * kSeqThreads + wave * kWave < chunks) {   // wave-uniform
+                res[j].opaque();
+                const HVec<CPG> acc = chunk_sum<Tw, CPG>(res[j], hs);
+                if (id < chunks) *reinterpret_cast<HVec<CPG> *>(part + id * CPG) = acc;
+            }
+        }
+        // the sentinel's stores are acknowledged (long ago) before h_t goes out, and the
+        // next step's input products set out: they are back before the next poll, which
+        // would wait for them (loads return in order)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        load_u(t + 1 < A.T ? t + 1 : t, ug_next);
+        __syncthreads();
+        // a row's chunks in ascending order, four lanes (one per gate) to a unit
         float sum[kItems];
 #pragma unroll
-        for (int s = 0; s < kItems; ++s) sum[s] = 0.0f;
-        for (int base = 0; base < chunks; base += kRes * kSeqThreads) {   // uniform
-            if (base > 0) __syncthreads();                   // part has been read
-            const int left = chunks - base;
-            gather(base, left < kRes * kSeqThreads ? left : kRes * kSeqThreads);
-            if (base == 0) {
-                // the sentinel's stores are acknowledged (long ago) before h_t goes out,
-                // and the next step's input products set out: they are back before the
-                // next poll, which would wait for them (loads return in order)
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                load_u(t + 1 < A.T ? t + 1 : t, ug_next);
-            }
-            __syncthreads();
-            // a row's chunks in ascending order, four lanes (one per gate) to a unit
-            const int end = base + kRes * kSeqThreads;
+        for (int s = 0; s < kItems; ++s) {
+            sum[s] = 0.0f;
+            const int it = tid + s * kSeqThreads;
+            if (it < items) {
+                const int cell = it >> 2;
+                const int r = (cell / CPG) * 4 + (it & 3);
+                const int b = cbeg[r], e = cbeg[r + 1];
+                const float *p = part + (cell % CPG);
+                for (int k = b; k < e; k += 8) {             // 8 loads in flight
+                    float v[8];
 #pragma unroll
-            for (int s = 0; s < kItems; ++s) {
-                const int it = tid + s * kSeqThreads;
-                if (it < items) {
-                    const int cell = it >> 2;
-                    const int r = (cell / CPG) * 4 + (it & 3);
-                    int b = cbeg[r], e = cbeg[r + 1];
-                    b = b > base ? b : base;
-                    e = e < end ? e : end;
-                    const float *p = part + (cell % CPG);
-                    for (int k = b; k < e; k += 8) {         // 8 loads in flight
-                        float v[8];
+                    for (int i = 0; i < 8; ++i) v[i] = p[(k + i < e ? k + i : e - 1) * CPG];
 #pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            v[i] = p[((k + i < e ? k + i : e - 1) - base) * CPG];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) sum[s] += k + i < e ? v[i] : 0.0f;
-                    }
+                    for (int i = 0; i < 8; ++i) sum[s] += k + i < e ? v[i] : 0.0f;
                 }
             }
         }
@@ -462,44 +467,6 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
                 }
             }
         }
-    }
-    return true;
-    };
-    bool ok;
-    if (chunks <= kRes * kSeqThreads) {                      // uniform
-        // all of them in registers for the whole sequence
-        Chunk<Tw> res[kRes];
-#pragma unroll
-        for (int j = 0; j < kRes; ++j) {
-            const int id = tid + j * kSeqThreads;
-            fetch(res[j], id < chunks ? id : chunks - 1);
-        }
-        ok = steps([&](int, int n) {
-#pragma unroll
-            for (int j = 0; j < kRes; ++j) {
-                const int id = j * kSeqThreads + tid;
-                if (j * kSeqThreads + wave * kWave < n) {    // wave-uniform
-                    res[j].opaque();
-                    const HVec<CPG> acc = chunk_sum<Tw, CPG>(res[j], hs);
-                    if (id < n) *reinterpret_cast<HVec<CPG> *>(part + id * CPG) = acc;
-                }
-            }
-        });
-    } else {
-        // more than fit (dense rows, wide layers): each is read again at each step
-        ok = steps([&](int base, int n) {
-#pragma unroll 1
-            for (int id = tid; id < n; id += kSeqThreads) {
-                Chunk<Tw> c;
-                fetch(c, base + id);
-                *reinterpret_cast<HVec<CPG> *>(part + id * CPG) = chunk_sum<Tw, CPG>(c, hs);
-            }
-        });
-    }
-    if (!ok) {
-        if (tid == 0)
-            __hip_atomic_store(A.failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
     }
     // the final cell state waits in the one slot that nobody reads any more (h_{T-2} is in
     // slot (T-2) % 3 and h_{T-1} in (T-1) % 3); the initial state stays as it was
@@ -614,10 +581,14 @@ bool seq_plan(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, SeqPlan
     p.groups = int((batch + p.cpg - 1) / p.cpg);
     // h's addresses in LDS are kept in 16 bits
     if ((H + 1) * p.cpg * 4 > 65536) return false;
-    p.units = int((H + kSeqMembers - 1) / kSeqMembers);
+    p.units = int(lstm_units(H));
     p.members = int((H + p.units - 1) / p.units);
     // a member's rows have a thread each, its (row, column) sums at most two per thread
     if (4 * p.units > kSeqMaxRows || 4 * p.units * p.cpg > 2 * kSeqThreads) return false;
+    // every member's weights stay in its registers: a form that read those past them again
+    // at each step took 33 us a step (H = 1500, batch 20, fp16, 6.5 % kept, 10 of 32 members
+    // past the limit) and 50 us (H = 2048, batch 32, 5 %), a launch per step 11.6 and 14.4
+    if (whh.lstm_chunks > seq_resident(p.cpg) * kSeqThreads) return false;
     // the kernels' 32-bit offsets into the input products
     if (4 * H * T * batch >= (int64_t(1) << 30)) return false;
     // the ring and the flag live in the workspace's last 4 * H * batch floats
@@ -737,3 +708,10 @@ hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
 }
 
 }  // namespace darb
+
+int64_t darb_test_lstm_chunks(const darb_plan *whh) { return whh->lstm_chunks; }
+
+int darb_test_lstm_seq_applies(const darb_plan *whh, int64_t H, int64_t T, int64_t batch,
+                               void *stream) {
+    return darb::lstm_seq_applies(*whh, H, T, batch, static_cast<hipStream_t>(stream)) ? 1 : 0;
+}

@@ -48,6 +48,35 @@ __device__ __forceinline__ int row_log2b_counts(int64_t c, int64_t N, int64_t M,
     return l < lmin ? lmin : (l > lmax ? lmax : l);
 }
 
+// The LSTM sequence launch needs to know, before it is chosen, the most chunks that one of
+// its workgroups would hold.  The wave's rows (one per active lane, block size 2^l) add
+// theirs to their members' in `held` (LDS, zeroed): consecutive rows have few members, so
+// a member at a time and one atomic each...
+__device__ __forceinline__ void lstm_hold(int (&held)[kLstmMembers], int64_t N, int64_t r, int l,
+                                          bool active) {
+    const int member = int(uint32_t(r) % uint32_t(N) / uint32_t(lstm_units(N)));
+    for (uint64_t left = __ballot(active); left != 0;) {     // wave-uniform
+        const int m = __builtin_amdgcn_readlane(member, __ffsll((unsigned long long)left) - 1);
+        const uint64_t same = __ballot(active && member == m);
+        int sum = 0;
+#pragma unroll
+        for (int v = 0; v < kGroups; ++v)
+            sum += __popcll(__ballot(l == v) & same) * int(lstm_row_chunks(N, v));
+        if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&held[m], sum);
+        left &= ~same;
+    }
+}
+// ... and the largest of them, for every lane of the calling wave.
+__device__ __forceinline__ int64_t lstm_most(const int (&held)[kLstmMembers]) {
+    int v = held[threadIdx.x & (kLstmMembers - 1)];
+#pragma unroll
+    for (int m = kLstmMembers / 2; m >= 1; m >>= 1) {
+        const int o = __shfl_xor(v, m, kWave);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
 // Rank of this lane among the wave's active lanes below it with the same key, and
 // the wave's count per key (every lane of the wave gets the same counts).
 __device__ __forceinline__ int wave_rank(int key, bool active, int (&count)[kGroups]) {
@@ -89,13 +118,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_sizes_kernel(
 
 // One workgroup: group sizes and starts, and each workgroup's first position in each
 // group (overwriting wg_counts).  summary: rows, first_row, first_elem, first_word,
-// 8 int64 each.
+// 8 int64 each, and the LSTM chunks.
 __global__ __launch_bounds__(kPlanThreads) void plan_scan_kernel(
-    int64_t N, int64_t nwg, int32_t *__restrict__ wg_counts, int64_t *__restrict__ summary) {
+    int64_t M, int64_t N, int64_t nwg, const int64_t *__restrict__ rowinfo,
+    int32_t *__restrict__ wg_counts, int64_t *__restrict__ summary) {
     __shared__ int64_t total[kGroups];
     __shared__ int64_t start[kGroups];
+    __shared__ int held[kLstmMembers];
     const int v = threadIdx.x / kWave;                   // one wave per group
     const int lane = threadIdx.x & (kWave - 1);
+    if (threadIdx.x < kLstmMembers) held[threadIdx.x] = 0;
+    __syncthreads();
+    if (lstm_shape(M, N))                                // uniform; few rows
+        for (int64_t r0 = 0; r0 < M; r0 += kPlanThreads) {
+            const int64_t r = r0 + threadIdx.x;
+            lstm_hold(held, N, r, int(rowinfo[r < M ? r : M - 1] & 0xFF), r < M);
+        }
     if (v < kGroups) {
         // rows of group v, summed in chunks of 64 workgroups
         int64_t s = 0;
@@ -104,6 +142,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scan_kernel(
         if (lane == 0) total[v] = s;
     }
     __syncthreads();
+    if (v == kGroups) {
+        const int64_t most = lstm_most(held);
+        if (lane == 0) summary[kSummaryLstm] = most;
+    }
     if (threadIdx.x == 0) {
         int64_t row = 0, elem = 0, word = 0;
         for (int g = 0; g < kGroups; ++g) {
@@ -112,7 +154,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scan_kernel(
             summary[g] = total[g];
             summary[kGroups + g] = row;
             summary[2 * kGroups + g] = elem;
-            summary[3 * kGroups + g] = word;
+            if (g > 0) summary[3 * kGroups + g] = word;
             row += total[g];
             elem += total[g] * nblk;
             word += (total[g] * nblk + 31) / 32 * g;
@@ -147,13 +189,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
     constexpr int kPer = (kParts + kWave - 1) / kWave;   // of them per lane of the scan
     __shared__ int part[kGroups][kParts];                // rows of each pair, then the rows before
     __shared__ int64_t total[kGroups], first_row[kGroups], first_elem[kGroups];
+    __shared__ int held[kLstmMembers];
     const int lane = int(threadIdx.x) & (kWave - 1);
     const int wave = int(threadIdx.x) / kWave;
+    const bool lstm = lstm_shape(M, N);                  // uniform
     int64_t c[TILES];
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {                    // all loads first
         const int64_t r = int64_t(t) * kPlanThreads + threadIdx.x;
         c[t] = counts[r < M ? r : M - 1];
+    }
+    if (lstm) {
+        if (threadIdx.x < kLstmMembers) held[threadIdx.x] = 0;
+        __syncthreads();
     }
     int l[TILES], rank[TILES];
 #pragma unroll
@@ -166,6 +214,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
 #pragma unroll
             for (int v = 0; v < kGroups; ++v) part[v][t * kPlanWaves + wave] = cnt[v];
         }
+        if (lstm) lstm_hold(held, N, r, l[t], r < M);
     }
     __syncthreads();
     if (wave < kGroups) {                                // one wave per group
@@ -191,9 +240,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
         }
         if (lane == kWave - 1) total[wave] = incl;
     }
+    __shared__ int64_t most;
+    if (wave == kGroups) most = lstm ? lstm_most(held) : 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         int64_t row = 0, elem = 0, word = 0;
+        host->v[kSummaryLstm] = most;
         for (int g = 0; g < kGroups; ++g) {
             const int64_t nblk = (N + (int64_t(1) << g) - 1) >> g;
             first_row[g] = row;
@@ -201,7 +253,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
             host->v[g] = total[g];
             host->v[kGroups + g] = row;
             host->v[2 * kGroups + g] = elem;
-            host->v[3 * kGroups + g] = word;
+            if (g > 0) host->v[3 * kGroups + g] = word;
             row += total[g];
             elem += total[g] * nblk;
             word += (total[g] * nblk + 31) / 32 * g;
@@ -281,8 +333,8 @@ hipError_t launch_plan_device(int64_t M, int64_t N, const int64_t *counts, int64
     int32_t *wg_counts = reinterpret_cast<int32_t *>(summary + 4 * kGroups);
     hipLaunchKernelGGL(plan_sizes_kernel, dim3(unsigned(nwg)), dim3(kPlanThreads), 0, s, M, N,
                        counts, kept, mode, lmin, lmax, rowinfo, wg_counts);
-    hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(kPlanThreads), 0, s, N, nwg, wg_counts,
-                       summary);
+    hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(kPlanThreads), 0, s, M, N, nwg, rowinfo,
+                       wg_counts, summary);
     hipLaunchKernelGGL(plan_place_kernel, dim3(unsigned(nwg)), dim3(kPlanThreads), 0, s, M, N,
                        wg_counts, summary, rowinfo, perm);
     return hipGetLastError();
