@@ -327,10 +327,11 @@ int darb_prune_counts_noalloc(int64_t M, int64_t N, int wdtype, const void *W, i
  * rows of at most 512 retained weights, no stream capture, H of 16 to 4095 at batch <= 16,
  * 2048 at batch <= 32, 1024 at batch <= 64, and W_hh's weights in the workgroups'
  * registers: the ceil(H / 32) units of each (of 32) hold at most 1536 chunks of 16 weights
- * (1024 at batch > 32), each gate row in whole chunks.  Such launches follow each other on a device whatever their streams;
- * a workgroup's waits are bounded, and a sequence whose workgroups could not all run at
- * once (another process holding the device) is computed again without waiting, with the
- * same result bit for bit.  Otherwise each time step is one launch: a workgroup per
+ * (1024 at batch > 32), each gate row in whole chunks.  Such launches take turns on a
+ * device, each once all that its own stream ordered before it has ended; a workgroup's
+ * waits are bounded, and a sequence whose workgroups could not all run at once (another
+ * process holding the device) is computed again without waiting, with the same result bit
+ * for bit.  Otherwise each time step is one launch: a workgroup per
  * hidden unit computes the unit's four gate rows of W_hh h_{t-1} and the cell
  * (batch <= 64 and a multiple of 4, or batch <= 16; W_hh rows of at most 512
  * retained weights); other shapes run

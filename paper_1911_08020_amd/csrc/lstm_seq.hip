@@ -21,9 +21,14 @@
 // slot for h_{t+1} cannot see the old h_{t-2}.
 //
 // Waiting is bounded.  All members must be on the chip at once: the grid is at most one
-// workgroup per CU, and the host lets these launches follow each other on a device,
-// whatever their streams.  Other kernels hold CUs only until they end; another process
-// could hold them for longer.  A member that has polled max_polls times for one step sets
+// workgroup per CU, and sequences take turns on a device, whatever their streams.  The
+// turn is taken on the device, by the launch before the sequence, which then has all that
+// its stream ordered before it behind it: who holds the turn waits for nobody else, so a
+// sequence never waits for work that another stream has only queued.  (Ordered by the host
+// with events, a layer waited for one queued earlier on another stream and with it for
+// whatever that stream waited for, which could be this layer's own results.)  Other
+// kernels hold CUs only until they end; another process could hold them for longer.  A
+// member that has polled max_polls times for one step sets
 // the failure flag and leaves, the others follow, and the last launch
 // (lstm_finish_kernel) then computes the sequence again from the untouched initial
 // state, one workgroup per batch column, which needs nobody else.  It sums in the same
@@ -54,7 +59,8 @@ constexpr int kSeqMaxRows = kSeqThreads;   // gate rows of a member: one thread 
 constexpr int kSeqMaxNblk = 512;      // retained weights per row (at most 64 chunks)
 constexpr uint32_t kSentinel = 0x7FDA5EEDu;   // a quiet NaN
 constexpr int64_t kSeqMaxLds = 128 * 1024;
-constexpr int kMaxDevices = 64;
+// reads of the turn, about 2 us each, before a sequence runs without it
+constexpr uint32_t kTurnPolls = 1u << 22;
 constexpr int kFinishThreads = 1024;
 constexpr int kXccId = 20 | (31 << 11);       // s_getreg: all of the XCC_ID register
 
@@ -67,7 +73,7 @@ struct SeqArgs {
     float *h_seq;            // [H x ldu]
     float *h_out, *c_out;    // [H x batch]: written by the last launch only
     uint32_t *ring;          // [3][groups][H][CPG]
-    uint32_t *failed;
+    uint32_t *failed;        // [0]: a member gave up; [1]: the sequence holds the turn
     int64_t ldu;
     int32_t H, T, batch, groups, members, units;   // units per member
     uint32_t max_polls;
@@ -476,13 +482,35 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
         out[i] = __builtin_bit_cast(uint32_t, cst[i]);
 }
 
-// The sentinel into every slot, and no failure.
+// 1 while a sequence of this process has its turn on the device.
+__device__ uint32_t seq_turn;
+
+// The sentinel into every slot, no failure, and the turn: one lane waits for it while the
+// holder runs to its end.  The wait is bounded too; without the turn the sequence is still
+// right, since its members' waits are bounded, only slower if another has the CUs.
 __global__ __launch_bounds__(256) void lstm_seq_init_kernel(uint32_t *ring, int64_t words,
                                                             uint32_t *failed) {
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < words;
          i += int64_t(gridDim.x) * 256)
         ring[i] = kSentinel;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *failed = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        failed[0] = 0u;
+        uint32_t mine = 0u;
+        for (uint32_t polls = 0; polls < kTurnPolls; ++polls) {
+            if (atomicCAS(&seq_turn, 0u, 1u) == 0u) {
+                mine = 1u;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(32);
+        }
+        failed[1] = mine;
+    }
+}
+
+// The turn goes back (by the holder alone).
+__device__ __forceinline__ void seq_turn_over(const SeqArgs &A) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && A.failed[1] != 0u)
+        __hip_atomic_store(&seq_turn, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The final state into the caller's buffers.  After a failure: the whole sequence of batch
@@ -494,7 +522,8 @@ __global__ __launch_bounds__(kFinishThreads) void lstm_finish_kernel(SeqArgs A, 
     const int n = int(blockIdx.x);
     const int tid = int(threadIdx.x);
     const int H = A.H;
-    if (*A.failed == 0u) {                                   // uniform
+    if (A.failed[0] == 0u) {                                 // uniform
+        seq_turn_over(A);                                    // every member has left
         const uint32_t *c = A.ring + int64_t(A.T % 3) * A.groups * H * cpg +
                             int64_t(n / cpg) * H * cpg + n % cpg;
         for (int u = tid; u < H; u += kFinishThreads) {
@@ -557,6 +586,7 @@ __global__ __launch_bounds__(kFinishThreads) void lstm_finish_kernel(SeqArgs A, 
         A.h_out[int64_t(u) * A.batch + n] = h[u];
         A.c_out[int64_t(u) * A.batch + n] = c[u];
     }
+    seq_turn_over(A);        // only now: these workgroups held CUs that the next one needs
 }
 
 struct SeqPlan {
@@ -572,8 +602,7 @@ bool seq_plan(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, SeqPlan
     // against 159 for T = 32; 91 / 90 and 217 / 324 at H = 1024
     if (T < 16 || batch > 64 || H < 16 || T > 0x7FFFFFFF) return false;
     // one workgroup per CU, an XCD's 32 for each group
-    if (whh.cus < kSeqXcds * kSeqMembers || whh.device < 0 || whh.device >= kMaxDevices)
-        return false;
+    if (whh.cus < kSeqXcds * kSeqMembers) return false;
     for (int g = 0; g < whh.bins.nbins; ++g)
         if (whh.bins.nblk[g] > kSeqMaxNblk) return false;
     p.cpg = batch <= 8 ? 1 : batch <= 16 ? 2 : batch <= 32 ? 4 : 8;
@@ -591,7 +620,7 @@ bool seq_plan(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, SeqPlan
     if (whh.lstm_chunks > seq_resident(p.cpg) * kSeqThreads) return false;
     // the kernels' 32-bit offsets into the input products
     if (4 * H * T * batch >= (int64_t(1) << 30)) return false;
-    // the ring and the flag live in the workspace's last 4 * H * batch floats
+    // the ring and the flags live in the workspace's last 4 * H * batch floats
     if (3 * H * p.groups * p.cpg + 16 > 4 * H * batch) return false;
     const size_t hs = (size_t(H + 1) * p.cpg * 4 + 15) & ~size_t(15);
     p.lds = hs + size_t(kSeqThreads) * seq_resident(p.cpg) * p.cpg * 4 + size_t(kSeqMaxRows) * 8 +
@@ -600,41 +629,16 @@ bool seq_plan(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, SeqPlan
     return int64_t(p.lds) <= kSeqMaxLds && int64_t(p.finish_lds) <= kSeqMaxLds;
 }
 
-// The device's launches of lstm_seq_kernel one after the other, whatever their streams:
-// two that share the CUs half and half would wait for members that cannot start.  Under
-// the lock, a launch on another stream than the last one's waits for that one's event.
-struct SeqGate {
-    std::mutex mu;
-    hipEvent_t done[kMaxDevices] = {};
-    hipStream_t last[kMaxDevices] = {};
-
-    template <typename F> hipError_t pass(int dev, hipStream_t s, F &&launch) {
-        std::lock_guard<std::mutex> lock(mu);
-        hipError_t e = hipSuccess;
-        if (!done[dev]) {
-            e = hipEventCreateWithFlags(&done[dev], hipEventDisableTiming);
-            if (e != hipSuccess) {
-                done[dev] = nullptr;
-                return e;
-            }
-        } else if (last[dev] != s) {
-            e = hipStreamWaitEvent(s, done[dev], 0);
-            if (e != hipSuccess) return e;
-        }
-        launch();
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        last[dev] = s;
-        return hipEventRecord(done[dev], s);
-    }
-};
-
-SeqGate gate;                                 // its events live until the process ends
+// A call's three launches follow each other without another call's between them: on
+// streams that share a hardware queue, a wait for the turn in between would hold up the
+// launch that gives it back.
+std::mutex launch_order;
 
 template <typename Tw>
-hipError_t launch_seq_t(const SeqPlan &p, const SeqArgs &a, int dev, hipStream_t s) {
+hipError_t launch_seq_t(const SeqPlan &p, const SeqArgs &a, hipStream_t s) {
     const int64_t words = int64_t(3) * p.groups * a.H * p.cpg;
     const int64_t init = (words + 255) / 256 < 256 ? (words + 255) / 256 : 256;
+    std::lock_guard<std::mutex> lock(launch_order);
     hipLaunchKernelGGL(lstm_seq_init_kernel, dim3(unsigned(init)), dim3(256), 0, s, a.ring, words,
                        a.failed);
     const dim3 grid(unsigned(kSeqXcds * p.members));
@@ -648,19 +652,21 @@ hipError_t launch_seq_t(const SeqPlan &p, const SeqArgs &a, int dev, hipStream_t
             hipLaunchKernelGGL((lstm_seq_kernel<Tw, C, 2>), grid, dim3(kSeqThreads), p.lds,   \
                                s, a);                                                         \
     } while (0)
-    const hipError_t e = gate.pass(dev, s, [&] {
-        switch (p.cpg) {
-            case 1: DARB_SEQ(1); break;
-            case 2: DARB_SEQ(2); break;
-            case 4: DARB_SEQ(4); break;
-            default: DARB_SEQ(8); break;
-        }
-    });
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;                // nothing was launched
+    switch (p.cpg) {
+        case 1: DARB_SEQ(1); break;
+        case 2: DARB_SEQ(2); break;
+        case 4: DARB_SEQ(4); break;
+        default: DARB_SEQ(8); break;
+    }
 #undef DARB_SEQ
-    if (e != hipSuccess) return e;
+    e = hipGetLastError();
+    // also after an error: it gives the turn back
     hipLaunchKernelGGL((lstm_finish_kernel<Tw>), dim3(unsigned(a.batch)), dim3(kFinishThreads),
                        p.finish_lds, s, a, p.cpg);
-    return hipGetLastError();
+    const hipError_t last = hipGetLastError();
+    return e != hipSuccess ? e : last;
 }
 
 }  // namespace
@@ -668,7 +674,8 @@ hipError_t launch_seq_t(const SeqPlan &p, const SeqArgs &a, int dev, hipStream_t
 bool lstm_seq_applies(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, hipStream_t s) {
     SeqPlan p;
     if (!seq_plan(whh, H, T, batch, p)) return false;
-    // a captured launch replays where the host cannot order it after others
+    // not into a graph: branches that share a hardware queue may place a wait for the turn
+    // before the launch that gives it back
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
@@ -703,8 +710,8 @@ hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
     a.members = p.members;
     a.units = p.units;
     a.max_polls = max_polls;
-    if (wdtype == DARB_F32) return launch_seq_t<float>(p, a, whh.device, s);
-    return launch_seq_t<__half>(p, a, whh.device, s);
+    if (wdtype == DARB_F32) return launch_seq_t<float>(p, a, s);
+    return launch_seq_t<__half>(p, a, s);
 }
 
 }  // namespace darb
