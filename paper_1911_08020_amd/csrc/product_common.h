@@ -882,12 +882,23 @@ template <typename Tw, int GM, bool PK, bool RUNS> struct PairLoad {
             for (int i = 0; i < GM; ++i) o[i] = OV::field(b, i, go);
         }
         if constexpr (GM > 1) {
-            for (int back = r.back; __any(back > 0); --back) {   // wave-uniform, rarely
-                const bool move = back > 0;
+            // down by `back`, a power of two at a time.  (A place at a time, up to GM - 1
+            // times over, and selecting between array elements instead of their values,
+            // which picks one element at a variable index, took longer than all else of a
+            // small launch: the LSTM step of 128 units, batch 1, 21.3 us.)
+            if (__any(r.back > 0)) {                         // wave-uniform, the last rows
 #pragma unroll
-                for (int i = 0; i + 1 < GM; ++i) {
-                    v[i] = move ? v[i + 1] : v[i];
-                    if constexpr (!PK) o[i] = move ? o[i + 1] : o[i];
+                for (int s = GM / 2; s >= 1; s /= 2) {
+                    const bool move = (r.back & s) != 0;
+#pragma unroll
+                    for (int i = 0; i + s < GM; ++i) {
+                        const float vi = v[i], vn = v[i + s];
+                        v[i] = move ? vn : vi;
+                        if constexpr (!PK) {
+                            const int oi = o[i], on = o[i + s];
+                            o[i] = move ? on : oi;
+                        }
+                    }
                 }
             }
         }
@@ -927,7 +938,9 @@ __device__ __forceinline__ void spmm_tile(
     // windows take more registers); a 64-lane row's step already spans 64 weights
     constexpr int DEPTH = (L >= kWave || GM >= 4) ? 1 : (PK ? 2 : 4) / GM;
     constexpr int T = DEPTH * S;                          // weights per row per round
-    constexpr int NB = kSpmmBatch;                        // X-row gathers in flight per lane
+    // X-row gathers in flight per lane; twice as many at one lane per row, where a batch
+    // ends after half a step otherwise (512 x 4096 fp32, B = 1: 15.4 us)
+    constexpr int NB = L == 1 ? 2 * kSpmmBatch : kSpmmBatch;
     static_assert(S % NB == 0, "a gather batch lies inside one step");
 
     const int g = block_group(sch, tile);
@@ -1040,12 +1053,15 @@ __device__ __forceinline__ void spmm_tile(
     // software pipelined: the pairs of round i + 1 load while round i gathers
     auto run = [&](auto runs) {
         using PL = PairLoad<Tw, GM, PK, decltype(runs)::value>;
-        typename PL::Raw raw[DEPTH];
-        // lanes past the share or the rows load a slot of their row block that exists and
-        // are masked when settled
+        typename PL::Raw raw[DEPTH] = {};
+        // lanes past the share or the rows load a slot of their row block that exists, or
+        // keep what an earlier step held, and are masked when settled
         auto issue_round = [&](int k0) {
 #pragma unroll
             for (int st = 0; st < DEPTH; ++st) {
+                // a step past the share loads nothing (wave-uniform; 512 x 256 fp32,
+                // B = 16: 3.53 us with its loads, 3.36 so)
+                if (st > 0 && k0 + st * S >= kend) break;
                 const int k = k0 + st * S + sub * GM;
                 raw[st] = PL::issue(vr, go, j0, row_ok && k < kend ? k : kbeg, left);
             }
