@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kStepThreads) void lstm_step_kernel(
             float v[GM];
             int o[GM];
             using PL = PairLoad<Tw, GM, false, true>;
-            PL::decode(PL::issue(values + r0, go, r0, ok ? k : k0, nnz - r0), go, v, o);
+            PL::decode(PL::issue(values + r0, go, r0, ok ? k : k0, nnz - r0), go, 0u, v, o);
 #pragma unroll
             for (int gi = 0; gi < GM; ++gi) {
                 const bool okg = ok && k + gi < nblk;

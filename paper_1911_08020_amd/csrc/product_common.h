@@ -127,9 +127,10 @@ __device__ __forceinline__ int block_begin_of(const ProductSchedule &s, int g) {
 // Offset sources.  A lane loads the indices of NV consecutive retained weights of a
 // group (group slots j .. j + NV - 1, j a multiple of NV) as `Raw`, keeps them in
 // registers while other loads are in flight, turns them into `Bits` when it needs
-// them and reads index q with field().  row() and load_row() are the same for vector i of
-// a row that starts at a multiple of NV; for 8 packed indices the row's part of the
-// address is formed once.
+// them (j again: its low five bits) and reads index q with field().  row() and load_row()
+// are the same for vector i of a row that starts at a multiple of NV; for 8 packed indices
+// the row's part of the address is formed once.  fix<LB>() and field_c<LB>() are bits() and
+// field() for a block size fixed at compile time; j() gives j where it is needed.
 // ---------------------------------------------------------------------------------
 
 struct GroupOffsets {
@@ -167,13 +168,14 @@ template <int NV> struct Off<false, NV> {
     __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
         return load(go, r.j0 + int64_t(i) * NV);
     }
-    __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return r; }
+    __device__ static Bits bits(const Raw &r, const GroupOffsets &, uint32_t) { return r; }
+    template <int LB, typename J> __device__ static Raw fix(const Raw &r, J &&) { return r; }
     __device__ static int field(const Bits &b, int q, const GroupOffsets &) {
         if constexpr (NV <= 4) return int((uint32_t(b) >> (8 * q)) & 0xFFu);
         else return int((b[q >> 2] >> (8 * (q & 3))) & 0xFFu);
     }
     // the same with q a compile-time index (the block size is implied by the byte)
-    template <int LB> __device__ static int field_c(const Bits &b, int q) {
+    template <int LB> __device__ static int field_c(const Raw &b, int q) {
         return field(b, q, GroupOffsets{});
     }
 };
@@ -189,7 +191,12 @@ template <int NV> struct Off<true, NV> {
     __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
         return load(go, r.j0 + int64_t(i) * NV);
     }
-    __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return packed_bits32(r); }
+    __device__ static Bits bits(const Raw &r, const GroupOffsets &, uint32_t) {
+        return packed_bits32(r);
+    }
+    template <int LB, typename J> __device__ static Bits fix(const Raw &r, J &&) {
+        return packed_bits32(r);
+    }
     __device__ static int field(Bits b, int q, const GroupOffsets &go) {
         return packed_field(b, q, go.pk);
     }
@@ -212,12 +219,18 @@ template <> struct Off<true, 8> {
     __device__ static Raw load_row(const GroupOffsets &go, const Row &r, int i) {
         return packed_load8(go.pk, r.at, r.v, i);
     }
-    __device__ static Bits bits(const Raw &r, const GroupOffsets &) { return packed_bits64(r); }
+    __device__ static Bits bits(const Raw &r, const GroupOffsets &go, uint32_t j) {
+        return packed_bits64(r, go.pk, int(j >> 3) & 3);
+    }
     __device__ static int field(Bits b, int q, const GroupOffsets &go) {
         return packed_field(b, q, go.pk);
     }
-    template <int LB> __device__ static int field_c(Bits b, int q) {
-        return int(uint32_t(b >> (q * LB)) & ((1u << LB) - 1u));
+    template <int LB, typename J> __device__ static Raw fix(Raw r, J &&j) {
+        if constexpr (LB > 0 && LB < 4) r.lo >>= 8 * packed_back(LB, int(j() >> 3) & 3);
+        return r;
+    }
+    template <int LB> __device__ static int field_c(const Raw &r, int q) {
+        return packed_field_c<LB>(r, q);
     }
 };
 
@@ -231,8 +244,9 @@ template <> struct Off<true, 16> {
         return Raw{packed_load8(go.pk, at, int(j >> 3), 0),
                    packed_load8(go.pk, at, int(j >> 3), 1)};
     }
-    __device__ static Bits bits(const Raw &r, const GroupOffsets &) {
-        return Bits{packed_bits64(r.lo), packed_bits64(r.hi)};
+    __device__ static Bits bits(const Raw &r, const GroupOffsets &go, uint32_t j) {
+        const int oct = int(j >> 3) & 2;
+        return Bits{packed_bits64(r.lo, go.pk, oct), packed_bits64(r.hi, go.pk, oct + 1)};
     }
     __device__ static int field(const Bits &b, int q, const GroupOffsets &go) {
         return q < 8 ? packed_field(b.lo, q, go.pk) : packed_field(b.hi, q - 8, go.pk);
@@ -422,7 +436,7 @@ __global__ __launch_bounds__(kSpmvThreads) void spmv_kernel(
                 for (int t = 0; t < KV; ++t) {
                     const int vi = base + T.sub + t * T.L;
                     if (vi < T.nvec) {
-                        const typename OV::Bits ob = OV::bits(T.ov[t], T.go);
+                        const typename OV::Bits ob = OV::bits(T.ov[t], T.go, uint32_t(T.j0) + uint32_t(vi * VEC));
 #pragma unroll
                         for (int q = 0; q < VEC; ++q) {
                             const int c = ((vi * VEC + q) << T.lb) + OV::field(ob, q, T.go);
@@ -449,14 +463,14 @@ __global__ __launch_bounds__(kSpmvThreads) void spmv_kernel(
 #pragma unroll
                 for (int q = 0; q < VEC; ++q) {
                     const int k = vi * VEC + q;
-                    const int o = OS::field(OS::bits(OS::load(T.go, T.j0 + k), T.go), 0, T.go);
+                    const int o = OS::field(OS::bits(OS::load(T.go, T.j0 + k), T.go, 0u), 0, T.go);
                     acc = fmaf(to_f32<Tw>(vr[k]), xat((k << T.lb) + o), acc);
                 }
             }
         } else {
             const Tw *vr = values + T.e0;
             for (int k = T.sub; k < T.nblk; k += T.L) {
-                const int o = OS::field(OS::bits(OS::load(T.go, T.j0 + k), T.go), 0, T.go);
+                const int o = OS::field(OS::bits(OS::load(T.go, T.j0 + k), T.go, 0u), 0, T.go);
                 acc = fmaf(to_f32<Tw>(vr[k]), xat((k << T.lb) + o), acc);
             }
         }
@@ -686,7 +700,13 @@ __global__ __launch_bounds__(kSpmvThreads, 4) void spmv_rows_kernel(SpmvRowsArgs
             if (k < n) {
                 uint32_t bk = base + uint32_t(k) * stepk;
                 bk = bk < lastb ? bk : lastb;
-                const typename OV::Bits ob = OV::bits(ov[k], go);
+                // the vector's first slot, where the format asks for it
+                const auto ob = OV::template fix<LB>(ov[k], [&] {
+                    bool any;
+                    int vi = sub + k * L;
+                    vi = vi < nvec ? vi : nvec - 1;
+                    return (uint32_t(row_of(blk, any)) * uint32_t(nvec) + uint32_t(vi)) * VEC;
+                });
                 float xv[VEC];
 #pragma unroll
                 for (int q = 0; q < VEC; ++q) {
@@ -869,15 +889,16 @@ template <typename Tw, int GM, bool PK, bool RUNS> struct PairLoad {
         }
         return r;
     }
-    __device__ static void decode(const Raw &r, const GroupOffsets &go, float (&v)[GM],
-                                  int (&o)[GM]) {
+    // j: the low bits of the slot that was asked for, j0 + k
+    __device__ static void decode(const Raw &r, const GroupOffsets &go, uint32_t j,
+                                  float (&v)[GM], int (&o)[GM]) {
 #pragma unroll
         for (int i = 0; i < GM; ++i) v[i] = to_f32<Tw>(r.a.e[i]);
         if constexpr (kEach) {
 #pragma unroll
-            for (int i = 0; i < GM; ++i) o[i] = OS::field(OS::bits(r.ob.r[i], go), 0, go);
+            for (int i = 0; i < GM; ++i) o[i] = OS::field(OS::bits(r.ob.r[i], go, 0u), 0, go);
         } else {
-            const typename OV::Bits b = OV::bits(r.ob, go);
+            const typename OV::Bits b = OV::bits(r.ob, go, j);
 #pragma unroll
             for (int i = 0; i < GM; ++i) o[i] = OV::field(b, i, go);
         }
@@ -1074,7 +1095,7 @@ __device__ __forceinline__ void spmm_tile(
             for (int st = 0; st < DEPTH; ++st) {
                 float v[GM];
                 int o[GM];
-                PL::decode(raw[st], go, v, o);
+                PL::decode(raw[st], go, uint32_t(j0) + uint32_t(k0 + st * S + sub * GM), v, o);
                 settle(k0, st, v, o, vl, cl);
             }
             const int k1 = k0 + DEPTH * S;
@@ -1282,7 +1303,7 @@ __global__ __launch_bounds__(kXldsThreads) void spmm_xlds_kernel(
                 const int kn = k0 + kXldsStep < nblk ? k0 + kXldsStep : k0;
                 const Step16<Tw> w_next = load_w(e0 + kn);
                 const typename OV::Raw ob_next = load_o(go, j0 + kn);
-                const typename OV::Bits obits = OV::bits(ob, go);
+                const typename OV::Bits obits = OV::bits(ob, go, uint32_t(j0) + uint32_t(k0));
                 static_for<0, kXldsStep / kXldsBatch>([&](auto bc) {
                     constexpr int b0 = decltype(bc)::value * kXldsBatch;
                     f32x4 xv[kXldsBatch];
