@@ -1572,12 +1572,13 @@ hipError_t launch_spmv_form(const darb_plan &p, const void *values, const uint8_
     return launch_spmv_t<Tw, Tx, true>(p, values, nullptr, packed, x, y, scales, st);
 }
 
+// wide_lgl: log2 lanes per row for an X past 4 GiB, which has a few widths only
 inline bool spmm_schedule(const darb_plan &p, int64_t B, int cpl, ProductSchedule &s,
-                          bool wide = false) {
+                          int wide_lgl = -1) {
     s = ProductSchedule{};
     s.nbins = p.bins.nbins;
     const int64_t lanes = (B + cpl - 1) / cpl;        // lanes needed for all columns
-    int lgL = wide || lanes >= kWave ? 6 : ilog2_ceil(lanes);
+    int lgL = wide_lgl >= 0 ? wide_lgl : lanes >= kWave ? 6 : ilog2_ceil(lanes);
     if (p.nnz < 16 && lgL < 4) lgL = 4;               // no room for vectors of weights
     const int64_t slabs = (lanes + (int64_t(1) << lgL) - 1) >> lgL;
     if (slabs > 0x7FFFFFFF) return false;
@@ -1698,8 +1699,11 @@ hipError_t launch_spmm_t(const darb_plan &p, const void *values, const uint8_t *
     const bool dwords = reinterpret_cast<uintptr_t>(X) % 4 == 0 &&
                         (ldx * int64_t(sizeof(Tx))) % 4 == 0;
     const int64_t vec_lanes = int64_t(1) << ilog2_ceil((B + CPL - 1) / CPL);
-    const bool many = p.M * (vec_lanes < kWave ? vec_lanes : int64_t(kWave)) / kWave * kSpmmWaves >=
-                      16 * (p.cus > 0 ? p.cus : 256);
+    auto fills = [&](int64_t lanes) {                 // 16 waves per CU with so many per row
+        return p.M * (lanes < kWave ? lanes : int64_t(kWave)) / kWave * kSpmmWaves >=
+               16 * (p.cus > 0 ? p.cus : 256);
+    };
+    const bool many = fills(vec_lanes);
     int cpl = 1;
     if (dwords || sizeof(Tx) == 4) {
         if ((B + CPL - 1) / CPL > 4 && (B % CPL == 0 || many)) {
@@ -1710,22 +1714,38 @@ hipError_t launch_spmm_t(const darb_plan &p, const void *values, const uint8_t *
                 cpl *= 2;
         }
     }
-    // the gathers address X with 32-bit byte offsets; past 4 GiB a lane per column and 64
-    // lanes per row with 64-bit addresses, which gives the same sums
+    // the gathers address X with 32-bit byte offsets; past 4 GiB with 64-bit ones, the same
+    // sums, in five shapes: a wave of a column per lane where rows are few (256 rows of 4096
+    // columns, 5 %, fp32, B = 64: 10.6 us, 16.5 with 16 lanes of 16 bytes; 33 Mi columns,
+    // 64 rows, B = 16: 5.7 ms, and 6.4); from `many` rows on 8 or 16 lanes of a column or
+    // of 16 bytes (8192 rows, B = 64: 29.5 us, and 47.0 with a wave of columns)
     const int64_t most = int64_t(0xFFFFFFFF) / int64_t(sizeof(Tx));
     const bool wide = ldx > most || (p.N - 1) * ldx + B > most;
-    if (wide) cpl = 1;
+    int wide_lgl = -1;
+    if (wide) {
+        cpl = many && B > kRowLanes && (dwords || sizeof(Tx) == 4) ? CPL : 1;
+        if (cpl > 1) wide_lgl = (B + CPL - 1) / CPL > 8 ? 4 : 3;
+        else wide_lgl = B <= 8 && fills(8) ? 3 : B <= 16 && fills(16) ? 4 : 6;
+    }
     ProductSchedule s;
-    if (!spmm_schedule(p, B, cpl, s, wide))
+    if (!spmm_schedule(p, B, cpl, s, wide_lgl))
         return hipErrorInvalidConfiguration;
     if (s.block_begin[s.nbins] == 0) return hipSuccess;
     const Tw *v = static_cast<const Tw *>(values);
     const void *offs = offset_source(p, offsets, packed);
     const Tx *x = static_cast<const Tx *>(X);
     if (wide) {
-        hipLaunchKernelGGL((spmm_kernel<Tw, Tx, 1, 6, PK, true>), dim3(s.block_begin[s.nbins]),
-                           dim3(kSpmmThreads), 0, st, v, offs, x, ldx, B, Y, ldy, p.d_perm,
-                           int(p.N), p.bins, s, scales, p.nnz);
+        const int lgl = s.log2_lanes[0];
+#define DARB_WIDE(C, LGL)                                                                   \
+    hipLaunchKernelGGL((spmm_kernel<Tw, Tx, C, LGL, PK, true>), dim3(s.block_begin[s.nbins]),  \
+                       dim3(kSpmmThreads), 0, st, v, offs, x, ldx, B, Y, ldy, p.d_perm,        \
+                       int(p.N), p.bins, s, scales, p.nnz)
+        if (cpl > 1 && lgl == 3) DARB_WIDE(CPL, 3);
+        else if (cpl > 1) DARB_WIDE(CPL, 4);
+        else if (lgl == 3) DARB_WIDE(1, 3);
+        else if (lgl == 4) DARB_WIDE(1, 4);
+        else DARB_WIDE(1, 6);
+#undef DARB_WIDE
         return hipGetLastError();
     }
     if (cpl == 1)
