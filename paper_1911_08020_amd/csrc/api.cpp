@@ -759,7 +759,7 @@ static int lstm_steps(const darb_plan *whh, const void *whh_values, const uint8_
     const int64_t TB = T * batch;
     if (lstm_seq_applies(*whh, H, T, batch, s))
         return launched(launch_lstm_seq(*whh, wdtype, whh_values, whh_offsets, H, T, batch, U, G,
-                                        h_seq, h, c, kLstmMaxPolls, s), "lstm sequence");
+                                        h_seq, h, c, kLstmMaxPolls, false, s), "lstm sequence");
     if (lstm_step_fusable(*whh, batch, h, G)) {
         float *hb[2] = {h, G};
         for (int64_t t = 0; t < T; ++t) {

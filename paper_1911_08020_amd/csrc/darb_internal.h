@@ -130,13 +130,14 @@ hipError_t launch_lstm_step(const darb_plan &whh, int wdtype, const void *values
 // when lstm_seq_applies: U holds the input products [4H x T*batch], scratch 4*H*batch
 // floats (16-byte aligned); h and c are read, and written at the end.  A workgroup waits
 // for the others' part of a step at most max_polls reads (about half a microsecond each)
-// before the sequence is computed without waiting.
+// before the sequence is computed without waiting.  far: exchange h as workgroups on
+// different XCDs do, wherever they run.
 constexpr uint32_t kLstmMaxPolls = 1u << 16;
 bool lstm_seq_applies(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, hipStream_t s);
 hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
                            const uint8_t *offsets, int64_t H, int64_t T, int64_t batch,
                            const float *U, float *scratch, float *h_seq, float *h, float *c,
-                           uint32_t max_polls, hipStream_t s);
+                           uint32_t max_polls, bool far, hipStream_t s);
 hipError_t launch_lstm_cell(int64_t H, int64_t batch, const float *G, const float *U,
                             int64_t ldu, float *h, float *c, float *h_seq, int64_t ld_seq,
                             hipStream_t s);
@@ -166,8 +167,13 @@ hipError_t launch_stream_copy(void *dst, const void *src, int64_t bytes, hipStre
 
 }  // namespace darb
 
-// What the tests look at from outside (no part of the ABI): a plan's lstm_chunks, and
-// whether the LSTM layer's time steps would run as one launch.
+// What the tests reach from outside (no part of the ABI): launch_lstm_seq with its waiting
+// and its exchange chosen, a plan's lstm_chunks, and whether the LSTM layer's time steps
+// would run as one launch.
+extern "C" int darb_test_lstm_seq(const darb_plan *whh, int wdtype, const void *values,
+                                  const uint8_t *offsets, int64_t H, int64_t T, int64_t batch,
+                                  const float *U, float *scratch, float *h_seq, float *h,
+                                  float *c, uint32_t max_polls, int far, void *stream);
 extern "C" int64_t darb_test_lstm_chunks(const darb_plan *whh);
 extern "C" int darb_test_lstm_seq_applies(const darb_plan *whh, int64_t H, int64_t T,
                                           int64_t batch, void *stream);

@@ -8,13 +8,20 @@
 // Split.  The batch is cut into groups of CPG columns; a recurrence only couples units of
 // the same column, so groups never talk to each other.  Workgroup i belongs to group
 // i % 8 and the hardware hands workgroup i to XCD i % 8, so a group's members share one
-// XCD's L2, which is what makes the exchange of h cheap; nothing depends on it for
-// correctness.  A group's members split the hidden units evenly.
+// XCD's L2, which is what makes the exchange of h cheap.  Members compare the numbers of
+// the XCDs they run on before they rely on it.  A group's members split the hidden units
+// evenly.
 //
 // Exchange.  h_t goes through a ring of three slots in the workspace.  A slot starts out
 // filled with a sentinel (a NaN pattern that no stored h has) and a reader polls the data
 // itself until no word is the sentinel: one memory round trip per step, no separate flag.
-// Every word is written and read with device-scope atomics.  Having read all of h_{t-1},
+// Every word is read with a device-scope load.  It is written with a device-scope store
+// unless the whole group runs on one XCD: then with a plain one (workgroup scope), for
+// which the memory model promises other workgroups nothing.  What makes it right is the
+// hardware: the vector caches write through, so an acknowledged store is in the XCD's one
+// L2, and that is where the readers' loads go on the same XCD; equal XCC_ID registers are
+// therefore a condition of correctness.  The test forces the other form too and asks for
+// the same bits.  Having read all of h_{t-1},
 // a member knows that every other member has finished with h_{t-2} (it published h_{t-1}
 // after that), so it puts the sentinel back into its own part of that slot, waits until
 // this is acknowledged, and only then publishes h_t: whoever sees h_t and later polls the
@@ -77,6 +84,7 @@ struct SeqArgs {
     int64_t ldu;
     int32_t H, T, batch, groups, members, units;   // units per member
     uint32_t max_polls;
+    uint32_t far;            // device-scope stores wherever the members run
 };
 
 __device__ __forceinline__ int wave_uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -333,7 +341,7 @@ __global__ __launch_bounds__(kSeqThreads) void lstm_seq_kernel(SeqArgs A) {
         if (other) *far = 1;
         __syncthreads();
     }
-    const bool near = *far == 0;                             // uniform
+    const bool near = *far == 0 && A.far == 0u;              // uniform
     // A word of the ring.  On one XCD a plain store puts it where the readers look, the
     // L2 that they share (the vector caches write through); a device-scope store writes
     // it to memory and costs the readers a round trip to there (measured: 1.0 instead of
@@ -687,7 +695,7 @@ bool lstm_seq_applies(const darb_plan &whh, int64_t H, int64_t T, int64_t batch,
 hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
                            const uint8_t *offsets, int64_t H, int64_t T, int64_t batch,
                            const float *U, float *scratch, float *h_seq, float *h, float *c,
-                           uint32_t max_polls, hipStream_t s) {
+                           uint32_t max_polls, bool far, hipStream_t s) {
     SeqPlan p;
     if (!seq_plan(whh, H, T, batch, p)) return hipErrorInvalidConfiguration;
     SeqArgs a{};
@@ -710,11 +718,21 @@ hipError_t launch_lstm_seq(const darb_plan &whh, int wdtype, const void *values,
     a.members = p.members;
     a.units = p.units;
     a.max_polls = max_polls;
+    a.far = far ? 1u : 0u;
     if (wdtype == DARB_F32) return launch_seq_t<float>(p, a, s);
     return launch_seq_t<__half>(p, a, s);
 }
 
 }  // namespace darb
+
+int darb_test_lstm_seq(const darb_plan *whh, int wdtype, const void *values,
+                       const uint8_t *offsets, int64_t H, int64_t T, int64_t batch,
+                       const float *U, float *scratch, float *h_seq, float *h, float *c,
+                       uint32_t max_polls, int far, void *stream) {
+    return int(darb::launch_lstm_seq(*whh, wdtype, values, offsets, H, T, batch, U, scratch,
+                                     h_seq, h, c, max_polls, far != 0,
+                                     static_cast<hipStream_t>(stream)));
+}
 
 int64_t darb_test_lstm_chunks(const darb_plan *whh) { return whh->lstm_chunks; }
 

@@ -128,37 +128,38 @@ def test_lstm_sequence_launch(darb, case):
 
 
 @pytest.mark.parametrize("case", [(96, 16, 9, "f32", 4, 64, 0.1), (520, 17, 20, "f16", 4, 64, 0.1),
-                                  (512, 18, 18, "f32", 2, 8, 0.3)])
-def test_lstm_sequence_without_waiting(darb, case):
-    # a workgroup allowed no wait gives up at once and the last launch computes the
-    # sequence by itself: the same bits
+                                  (512, 18, 18, "f32", 2, 8, 0.3), (256, 40, 64, "f16", 4, 64, 0.1),
+                                  (130, 50, 3, "f32", 4, 64, 0.1)])
+def test_lstm_sequence_forms(darb, case):
+    # the exchange of workgroups on one XCD and on different ones; and a workgroup allowed no
+    # wait, which gives up at once, so that the last launch computes the sequence by itself:
+    # the same bits
     import ctypes
     H, T, B, dt, b_min, b_max, keep = case
-    say(f"lstm sequence recomputed {case}")
+    say(f"lstm sequence forms {case}")
     dtype = np.float32 if dt == "f32" else np.float16
     _, (_, (plan, v, o)), rng = _lstm_mats(darb, H, H, dtype, b_min, b_max, keep, 5)
     U = dev(rng.standard_normal((4 * H, T * B)).astype(np.float32))
     outs = []
-    for polls in (1 << 16, 0):
+    for polls, far in ((1 << 16, 0), (1 << 16, 1), (0, 0)):
         h = dev((0.5 * np.random.default_rng(1).standard_normal((H, B))).astype(np.float32))
         c = dev(np.random.default_rng(2).standard_normal((H, B)).astype(np.float32))
         seq = torch.zeros(H, T * B, device="cuda")
         scratch = torch.zeros(4 * H * B, device="cuda")
-        # darb::launch_lstm_seq (darb_internal.h), which the public call reaches with a limit
-        f = getattr(darb.lib(), "_ZN4darb15launch_lstm_seqERK9darb_planiPKvPKhlllPKfPfS9_S9_S9_j"
-                                "P12ihipStream_t")
         P = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
         I64 = ctypes.c_int64
-        rc = f(plan.handle, ctypes.c_int(0 if dt == "f32" else 1), P(v), P(o), I64(H), I64(T),
-               I64(B), P(U), P(scratch), P(seq), P(h), P(c), ctypes.c_uint32(polls),
-               ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        rc = darb.lib().darb_test_lstm_seq(
+            plan.handle, ctypes.c_int(0 if dt == "f32" else 1), P(v), P(o), I64(H), I64(T), I64(B),
+            P(U), P(scratch), P(seq), P(h), P(c), ctypes.c_uint32(polls), ctypes.c_int(far),
+            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
         assert rc == 0
         torch.cuda.synchronize()
         failed = int(scratch.view(torch.int32)[_seq_flag(H, B)])
         assert failed == (1 if polls == 0 else 0)
         outs.append((seq, h, c))
-    for a, b in zip(*outs):
-        assert torch.equal(a, b)
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert torch.equal(a, b)
 
 
 def _seq_flag(H, B):
