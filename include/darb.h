@@ -331,7 +331,7 @@ int darb_prune_counts_noalloc(int64_t M, int64_t N, int wdtype, const void *W, i
  * device, each once all that its own stream ordered before it has ended; a workgroup's
  * waits are bounded, and a sequence whose workgroups could not all run at once (another
  * process holding the device) is computed again without waiting, with the same result bit
- * for bit.  Otherwise each time step is one launch: a workgroup per
+ * for bit but some tens of milliseconds later.  Otherwise each time step is one launch: a workgroup per
  * hidden unit computes the unit's four gate rows of W_hh h_{t-1} and the cell
  * (batch <= 64 and a multiple of 4, or batch <= 16; W_hh rows of at most 512
  * retained weights); other shapes run

@@ -130,7 +130,8 @@ hipError_t launch_lstm_step(const darb_plan &whh, int wdtype, const void *values
 // when lstm_seq_applies: U holds the input products [4H x T*batch], scratch 4*H*batch
 // floats (16-byte aligned); h and c are read, and written at the end.  A workgroup waits
 // for the others' part of a step at most max_polls reads (about half a microsecond each)
-// before the sequence is computed without waiting.  far: exchange h as workgroups on
+// before the sequence is computed without waiting, which costs about as much as the longest
+// wait (some 30 ms; 40 for 200 steps of H = 1024, batch 32).  far: exchange h as workgroups on
 // different XCDs do, wherever they run.
 constexpr uint32_t kLstmMaxPolls = 1u << 16;
 bool lstm_seq_applies(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, hipStream_t s);
