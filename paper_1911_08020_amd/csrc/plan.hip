@@ -18,7 +18,9 @@
 // a plan are few enough that three launches, a copy and the wait for it cost several times
 // the work: 4096 rows, 5.0 + 2.6 + 3.4 us of kernels and 2.3 us of copy before, 8.3 us
 // now, and a compression of 4096 x 9216 fp32 (pruning, plan, encode, packing, codes) 158
-// -> 112 us, part of it from the pruning.  (Every thread fencing for itself: 12.4 us.)
+// -> 112 us, part of it from the pruning.  (Every thread fencing for itself: 12.4 us.)  The
+// whole call, host and all: 22.6 us at 4096 rows, 28.7 at 8192, 36.4 with three launches, and
+// 39 to 41 with 16 rows per thread at 10240 to 16384 rows.
 //
 // Otherwise three launches: per-row block size and per-workgroup group counts; one workgroup scans
 // those counts into group starts and each workgroup's first position per group (and
@@ -33,7 +35,7 @@ namespace {
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kGroups = kMaxBins;               // log2 b = 0 .. 7
-constexpr int64_t kPlanOneRows = 16 * kPlanThreads;
+constexpr int64_t kPlanOneRows = 8 * kPlanThreads;
 
 __device__ __forceinline__ int row_log2b_counts(int64_t c, int64_t N, int64_t M, int64_t kept,
                                                 int mode, int lmin, int lmax) {
@@ -270,8 +272,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_one_kernel(
             rowinfo[r] = ((first_elem[l[t]] + in_group * nblk) << 8) | l[t];
         }
     }
-    // every wave's table stores are in this XCD's L2 when the barrier lets go; the release
-    // then writes that back and sets the flag
+    // the barrier orders every wave's table stores before the flag's store, whose release at
+    // system scope is cumulative: it makes them visible too (the barrier itself waits for
+    // no other wave's stores)
     __syncthreads();
     if (threadIdx.x == 0)
         __hip_atomic_store(&host->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -319,7 +322,7 @@ hipError_t launch_plan_one(int64_t M, int64_t N, const int64_t *counts, int64_t 
     hipLaunchKernelGGL((plan_one_kernel<T>), dim3(1), dim3(kPlanThreads), 0, s, M, N, counts,  \
                        kept, mode, lmin, lmax, rowinfo, perm, host)
     if (M <= 4 * kPlanThreads) DARB_PLAN_ONE(4);
-    else DARB_PLAN_ONE(16);
+    else DARB_PLAN_ONE(8);
 #undef DARB_PLAN_ONE
     return hipGetLastError();
 }
