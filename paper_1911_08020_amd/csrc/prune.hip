@@ -20,10 +20,10 @@
 // last workgroup, only when some keys equal to t are not kept).
 //
 // From 5 Mi elements one pass streams all of W.  A sample of W (about 1/32) first
-// histograms finer first digits (the key's top 14 bits for fp32, 11 for fp16; the
-// same launch resets the state, and the count pass leaves the sample's histogram
-// at zero for the next call on the workspace), from
-// which the split pass's workgroups compute a bracket of them that holds the K-th
+// histograms finer first digits (the key's top 14 bits for fp32, 11 for fp16; from
+// 64 MiB of W on the same launch resets the state, and the count pass leaves the
+// sample's histogram at zero for the next call on the workspace; below that the
+// reset is a launch of its own), from which the split pass's workgroups compute a bracket of them that holds the K-th
 // key's, with a margin of six binomial standard deviations: as narrow as the
 // sample's statistics allow, not the width of one 11-bit digit.  The split pass
 // then counts, per row, the keys whose first digit is above the bracket (and their

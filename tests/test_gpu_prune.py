@@ -218,21 +218,33 @@ def test_fp16_sampled_bracket(darb, kind):
 
 
 def test_biased_sample_falls_back_to_w(darb):
-    # from 64 MiB the first digit's candidates come from a bracket proposed by a
-    # sample of W (ranges at a fixed stride); the split pass counts the keys above
-    # the bracket, and the threshold must lie between that count and it plus the
-    # candidates.  Rows exactly one sample stride long put every
-    # sampled range at the same columns (the first 1024, with the library's present
-    # sample); values spread over 20 octaves only there make the sample propose a
-    # narrow bracket near the top while the true threshold lies in the rest of W,
-    # so the check must send the later passes back to W, with the oracle's counts.
+    # the first digit's candidates come from a bracket proposed by a sample of W: pieces of
+    # 16 vectors of 4 fp32 keys, one every 32 pieces and 37 vectors.  Rows exactly one such
+    # stride long put every piece at the first 64 columns; values spread over 20 octaves
+    # only there propose a bracket near the top, while the threshold lies in the rest of W.
+    # The split pass counts the keys above the bracket, so the later passes must go back to
+    # W.  From 64 MiB on the sample's launch resets the state and relies on the last call
+    # for a zero histogram: three calls on one workspace, the last on an unbiased W.
     rng = np.random.default_rng(5)
-    M, N = 512, 32 * 1024 + 37 * 4
+    M, N = 7700, 32 * 64 + 37 * 4
     W = rng.uniform(0.0, 0.5, size=(M, N)).astype(np.float32)
-    W[:, :1024] = np.exp2(rng.uniform(0.0, 20.0, size=(M, 1024))).astype(np.float32)
+    W[:, :64] = np.exp2(rng.uniform(0.0, 20.0, size=(M, 64))).astype(np.float32)
     k = int(0.05 * M * N)
     say(f"biased sample: {M}x{N} fp32, k = {k}")
-    assert np.array_equal(gpu_counts(darb, dev(W), k), oracle.prune_counts(W, k))
+    assert W.nbytes >= 64 << 20
+    # the sample alone puts the threshold far above the true one: six standard deviations
+    # of its count do not reach it
+    seen = np.sort(W[:, :64].reshape(-1))[::-1]
+    true = np.partition(W.reshape(-1), M * N - k)[M * N - k]
+    at = 0.05 * seen.size
+    assert true < 0.5 < seen[int(at + 6 * np.sqrt(at) + 8)]
+    plain = rng.standard_normal((M, N)).astype(np.float32)
+    need = ctypes.c_int64()
+    assert darb.lib().darb_prune_workspace(M, N, 0, ctypes.byref(need)) == 0
+    ws = torch.zeros(need.value, dtype=torch.uint8, device="cuda")
+    for mat in (W, W, plain):
+        got = darb.prune_counts(dev(mat), k, workspace=ws)
+        assert np.array_equal(got.cpu().numpy(), oracle.prune_counts(mat, k))
 
 
 @pytest.mark.parametrize("case", ["candidates_fit", "candidate_room_overflows",
