@@ -285,7 +285,7 @@ int darb_spmm_i8(const darb_plan *plan, const int8_t *codes, const float *scales
  *   workspace  device, 256-byte aligned, >= the size darb_prune_workspace
  *              returns (about M*N/4 bytes: room for the keys whose leading digit
  *              lies in a small bracket around the threshold's, which the later
- *              passes read instead of W when W has 5 Mi elements or more); its
+ *              passes read instead of W from about 20 MiB of W on); its
  *              contents on entry do not change the counts (from 64 MiB of W a
  *              workspace last used by this call runs fastest: it leaves the part the
  *              next call's sample adds into at zero; other contents may cost that

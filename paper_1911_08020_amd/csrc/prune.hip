@@ -19,7 +19,7 @@
 // order, which for row counts means rows in ascending order (by the count pass's
 // last workgroup, only when some keys equal to t are not kept).
 //
-// From 5 Mi elements one pass streams all of W.  A sample of W (about 1/32) first
+// From 20 MiB of W (5 Mi elements of unaligned rows) one pass streams all of W.  A sample of W (about 1/32) first
 // histograms finer first digits (the key's top 14 bits for fp32, 11 for fp16; from
 // 64 MiB of W on the same launch resets the state, and the count pass leaves the
 // sample's histogram at zero for the next call on the workspace; below that the
@@ -42,7 +42,7 @@
 // has them (a few hundred per workgroup, added to an LDS histogram), so the pass after
 // it starts at the second: 4096 x 9216 fp32 59.7 -> 57.2 us.  The host launches as many
 // passes after the split as the key's digits need; a pass with nothing left to choose
-// hands the state on.  Below 5 Mi elements there is no sample and no split: a reset
+// hands the state on.  Below that there is no sample and no split: a reset
 // launch, then every pass streams W, which there costs less than the extra launches.  A
 // pass over the candidates runs only the workgroups they fill.  All state stays on the
 // device; nothing returns to the host between passes.
@@ -134,8 +134,12 @@ constexpr int kPieceLanes = 16;
 constexpr int kSampleLoads = 4;                     // vectors in flight per thread
 constexpr int kSampleGroups = 256;                  // workgroups of the sample pass
 constexpr int kCandPerThread = 8;                   // candidate passes: keys per thread
-// Elements of W from which the split pays: 2048 x 2048 fp32 takes 41.0 us without it and
-// 43.3 with it, 4096 x 2048 47.8 and 43.2, 4096 x 4096 fp16 53.7 and 47.4.
+// Bytes of W from which the split pays: 2048 x 2048 fp32 (16 MiB) takes 41.0 us without it
+// and 43.3 with it, 2622 x 2000 fp32 (20) 49.3 and 46.7, 4096 x 2048 fp16 (16) 48.0 and
+// 49.4, 4608 x 3072 fp16 (27) 56.4 and 54.2, 4096 x 4096 fp16 (32) 56.9 and 52.3.  Rows
+// that do not start on 16 bytes make a pass over W dearer: from 5 Mi elements on for them
+// (fp16, 6000 x 1500 58.0 and 54.9, 30000 x 300 120.5 and 110.0).
+constexpr int64_t kSplitMinBytes = int64_t(20) << 20;
 constexpr int64_t kSplitMinElems = int64_t(5) << 20;
 // Bytes of W from which the sample resets the state itself (and relies on the last call
 // for a zero histogram); below, the reset is a launch of its own, since a fresh workspace
@@ -1247,7 +1251,10 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
     if (init_blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     // the state reset: its own launch, unless the sample (the first kernel of a call
     // that splits) does it
-    const bool split = k > 0 && M * N >= kSplitMinElems;
+    const bool aligned = (reinterpret_cast<uintptr_t>(W) % 16 == 0) &&
+                         ((ldw * int64_t(sizeof(Bits))) % 16 == 0);
+    const bool split = k > 0 && (M * N * int64_t(sizeof(Bits)) >= kSplitMinBytes ||
+                                 (M * N >= kSplitMinElems && !aligned));
     const bool reset = !split || M * N * int64_t(sizeof(Bits)) < kResetInSample;
     if (reset)
         hipLaunchKernelGGL(prune_init_kernel, dim3(unsigned(init_blocks)), dim3(256), 0, s, M,
@@ -1255,8 +1262,6 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
                            w.fine);
     if (k == 0) return hipGetLastError();               // nothing kept: counts stay 0
 
-    const bool aligned = (reinterpret_cast<uintptr_t>(W) % 16 == 0) &&
-                         ((ldw * int64_t(sizeof(Bits))) % 16 == 0);
     // digits of the whole key (3 for fp32, 2 for fp16): every way through the
     // passes needs at most that many after the split
     constexpr int passes = digit_passes(Tr::KEY_BITS);
@@ -1278,7 +1283,7 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
         rd ^= 1;
     };
     // the split pass pays for its extra launches only on large matrices: below
-    // kSplitMinElems every pass streams W
+    // kSplitMinBytes (kSplitMinElems unaligned) every pass streams W
     if (split) {
         // the sample (one piece out of about kSampleEvery, the stride drifting by an odd
         // number of vectors so that it does not follow power-of-two rows), in as many

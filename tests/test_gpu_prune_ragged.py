@@ -32,10 +32,11 @@ def host(t):
     return t.cpu().numpy()
 
 
-# 5 Mi elements is where the sampled split begins: just below, just above, rows shorter
+# 20 MiB is where the sampled split begins: just below, just above (fp32, fp16), rows shorter
 # than a sampled piece, rows that start on any element, a leading dimension of its own
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
-@pytest.mark.parametrize("M,N,skip", [(2621, 2000, 0), (2622, 2000, 0), (5243, 1001, 0),
+@pytest.mark.parametrize("M,N,skip", [(2621, 2000, 0), (2622, 2000, 0), (5242, 2000, 0),
+                                      (5243, 2000, 0), (5243, 1001, 0),
                                       (1048600, 5, 0), (80000, 67, 1), (41, 131073, 3)])
 def test_prune_split_at_ragged_sizes(darb, dtype, M, N, skip):
     say(f"prune {M}x{N} {np.dtype(dtype).name} skip {skip}")
