@@ -124,13 +124,24 @@ __host__ __device__ constexpr int digit_passes(int hi) {
 constexpr int kSplitLds = 8192;                     // candidates a workgroup can hold
 constexpr int kWaveRoom = kSplitLds / kHistWaves;   // of which each of its waves' own
 constexpr int64_t kSampleEvery = 32;                // the sample reads about 1/32 of W
-constexpr int64_t kSampleDrift = 37;                // vectors added to the sample stride
-// The sample is taken in pieces of 16 vectors (256 bytes), so that nearly every row gives
-// its share of it: rows differ in density (that is what DARB adapts to), and ranges of
-// 4 KiB from an eighth of the rows missed the threshold by more than the margin every
+// The sample is taken in pieces of up to 16 vectors (256 bytes), so that nearly every row
+// gives its share of it: rows differ in density (that is what DARB adapts to), and ranges
+// of 4 KiB from an eighth of the rows missed the threshold by more than the margin every
 // second time on 8192 x 4096, where a miss costs four passes over W (170 us instead of
-// 60).
-constexpr int kPieceLanes = 16;
+// 60).  Rows that end before the next piece take smaller ones: 60000 x 129 fp32, rows
+// scaled by a log-normal, 30 % kept, 184 us with pieces of 16 (half a row, from every 17th
+// one), 85 so.
+constexpr int kLgPieceMost = 4, kLgPieceLeast = 1;
+// vectors from one piece to the next: about kSampleEvery pieces, and an odd number more, so
+// that the pieces do not follow power-of-two rows
+__host__ __device__ constexpr int64_t piece_step(int lg) {
+    return (kSampleEvery << lg) + 2 * (int64_t(1) << lg) + 5;
+}
+inline int lg_piece(int64_t row_vectors) {
+    int lg = kLgPieceMost;
+    while (lg > kLgPieceLeast && piece_step(lg) > row_vectors + row_vectors / 8) --lg;
+    return lg;
+}
 constexpr int kSampleLoads = 4;                     // vectors in flight per thread
 constexpr int kSampleGroups = 256;                  // workgroups of the sample pass
 constexpr int kCandPerThread = 8;                   // candidate passes: keys per thread
@@ -707,14 +718,14 @@ __global__ __launch_bounds__(kHistThreads) void prune_hist_kernel(
 
 // The first kernel of a call that splits: the state reset (as prune_init_kernel,
 // except `fine`, which the previous call's count left at zero), then the sample:
-// the histogram of the keys' first SAMPLE_BITS bits over pieces of kPieceLanes vectors
+// the histogram of the keys' first SAMPLE_BITS bits over pieces of 2^lg_piece vectors
 // piece_stride elements apart in W padded to whole vectors, added into `fine` (32-bit
 // totals: only
 // the bracket depends on them, and a bracket that misses the K-th key, as one from
 // a workspace that held something else would, costs passes over W, not exactness).
 template <typename Bits>
 __global__ __launch_bounds__(kHistThreads) void prune_sample_kernel(
-    const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t pieces,
+    const Bits *__restrict__ W, int64_t ldw, int64_t M, int64_t N, int64_t pieces, int lg_piece,
     int64_t piece_stride, uint32_t *__restrict__ fine, int64_t k, PruneState *slots,
     SplitInfo *info, int64_t *counts, int64_t *eq, int64_t *gt1, uint64_t *totals) {
     using Tr = PruneTraits<Bits>;
@@ -729,14 +740,15 @@ __global__ __launch_bounds__(kHistThreads) void prune_sample_kernel(
     const int64_t total = M * Np;
     const int64_t threads = int64_t(gridDim.x) * kHistThreads;
     const int64_t first = int64_t(blockIdx.x) * kHistThreads + threadIdx.x;
-    const int64_t vectors = pieces * kPieceLanes;
+    const int64_t vectors = pieces << lg_piece;
+    const int64_t in_piece = (int64_t(1) << lg_piece) - 1;
     PVec<Bits, VEC> v[kSampleLoads];
     int64_t left[kSampleLoads];                         // elements of the row from the vector on
     auto load = [&](int64_t i0) {
 #pragma unroll
         for (int u = 0; u < kSampleLoads; ++u) {
             const int64_t i = i0 + u * threads;
-            const int64_t e = (i / kPieceLanes) * piece_stride + (i % kPieceLanes) * VEC;
+            const int64_t e = (i >> lg_piece) * piece_stride + (i & in_piece) * VEC;
             const bool in = i < vectors && e < total;
             const int64_t ec = in ? e : 0;
             int64_t r = int64_t(double(ec) * inv);      // its row, or one off
@@ -1271,8 +1283,7 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
     // more predicted candidates than this and the split pass takes the first digit.  The
     // prediction is a count of thousands of sampled keys, good to a few percent: with half
     // the room allowed, three fine digits of a bracket were too many where values are dense
-    // at the threshold (4096 x 4096 fp32,
-    // uniform values, 30 % kept: 82.2 us, and 49.7 so)
+    // at the threshold (4096 x 4096 fp32, uniform values, 30 % kept: 82.2 us, and 49.7 so)
     const uint64_t cand_limit =
         std::min<uint64_t>(cap - cap / 8, uint64_t(groups) * uint64_t(kSplitLds) / 2);
     int rd = 0;                                         // the state slot the next kernel reads
@@ -1285,18 +1296,17 @@ hipError_t launch_prune_t(int64_t M, int64_t N, const void *Wv, int64_t ldw, int
     // the split pass pays for its extra launches only on large matrices: below
     // kSplitMinBytes (kSplitMinElems unaligned) every pass streams W
     if (split) {
-        // the sample (one piece out of about kSampleEvery, the stride drifting by an odd
-        // number of vectors so that it does not follow power-of-two rows), in as many
-        // workgroups as it has loads for; the split pass then reads W once
-        const int64_t piece = kPieceLanes * Tr::VEC;
-        const int64_t piece_stride = kSampleEvery * piece + kSampleDrift * Tr::VEC;
+        // the sample (one piece out of about kSampleEvery), in as many workgroups as it
+        // has loads for; the split pass then reads W once
+        const int lg = lg_piece(padded_n<Bits>(N) / Tr::VEC);
+        const int64_t piece_stride = piece_step(lg) * Tr::VEC;
         const int64_t pieces = (M * padded_n<Bits>(N) + piece_stride - 1) / piece_stride;
         const int64_t per_group = int64_t(kHistThreads) * kSampleLoads;
         const int64_t sample_groups =
-            std::min<int64_t>(kSampleGroups, (pieces * kPieceLanes + per_group - 1) / per_group);
+            std::min<int64_t>(kSampleGroups, ((pieces << lg) + per_group - 1) / per_group);
         hipLaunchKernelGGL((prune_sample_kernel<Bits>),
                            dim3(unsigned(std::max<int64_t>(1, sample_groups))),
-                           dim3(kHistThreads), 0, s, W, ldw, M, N, pieces, piece_stride, w.fine, k,
+                           dim3(kHistThreads), 0, s, W, ldw, M, N, pieces, lg, piece_stride, w.fine, k,
                            w.slots, w.info, counts, w.eq, w.gt1, w.totals);
         if (aligned)
             hipLaunchKernelGGL((prune_split_kernel<Bits, true>), dim3(groups), dim3(kHistThreads),

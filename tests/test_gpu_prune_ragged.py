@@ -37,7 +37,7 @@ def host(t):
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("M,N,skip", [(2621, 2000, 0), (2622, 2000, 0), (5242, 2000, 0),
                                       (5243, 2000, 0), (5243, 1001, 0),
-                                      (1048600, 5, 0), (80000, 67, 1), (41, 131073, 3)])
+                                      (1048600, 5, 0), (80000, 67, 1), (60000, 129, 0), (41, 131073, 3)])
 def test_prune_split_at_ragged_sizes(darb, dtype, M, N, skip):
     say(f"prune {M}x{N} {np.dtype(dtype).name} skip {skip}")
     rng = np.random.default_rng(M + N)
