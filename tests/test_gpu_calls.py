@@ -1,14 +1,12 @@
 """The native call module against the methods' Python code: the same results bit for bit
 (with buffers given or not, on a given stream, from strided operands), and what the Python
 code refuses stays refused with the same error."""
-import sys
-
 import numpy as np
 import pytest
 
-pytestmark = pytest.mark.gpu
+from tests._gpu import darb, say, torch  # noqa: F401
 
-torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
 
 
 class Plain(torch.Tensor):
@@ -19,19 +17,8 @@ def plain(t):
     return t.as_subclass(Plain)
 
 
-def say(*a):
-    print(*a, flush=True, file=sys.stderr)
-
-
 @pytest.fixture(scope="module")
-def darb():
-    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
-    import paper_1911_08020_amd as d
-    return d
-
-
-@pytest.fixture(scope="module")
-def fmt(darb):
+def fmt(darb):  # noqa: F811
     rng = np.random.default_rng(7)
     M, N, B = 70, 301, 6
     plan = darb.Plan(M, N, 1.0 / rng.choice([4, 8, 16], size=M), 0.1, 0, 4, 32).upload()
@@ -59,7 +46,7 @@ CALLS = {
 
 
 @pytest.mark.parametrize("name", sorted(CALLS))
-def test_native_call_equals_python_path(darb, fmt, name):
+def test_native_call_equals_python_path(darb, fmt, name):  # noqa: F811
     say(f"native call: {name}")
     call = CALLS[name]
     want = call(fmt, plain)
@@ -78,7 +65,7 @@ def test_native_call_equals_python_path(darb, fmt, name):
         assert torch.equal(call(fmt, lambda t: t), want.as_subclass(torch.Tensor))
 
 
-def test_native_encode_equals_python_path(darb, fmt):
+def test_native_encode_equals_python_path(darb, fmt):  # noqa: F811
     v, o = torch.empty_like(fmt["v"]), torch.empty_like(fmt["o"])
     got = fmt["plan"].encode(fmt["W"], values=v, offsets=o)
     assert got[0] is v and got[1] is o
@@ -102,7 +89,7 @@ def test_native_encode_equals_python_path(darb, fmt):
     (lambda f: f["plan"].spmv_i8(f["q"], f["s"], f["x"], offsets=f["o"], packed=f["p"]), ValueError),
     (lambda f: f["plan"].encode(f["W"], values=f["v"].half(), offsets=f["o"]), TypeError),
     (lambda f: f["plan"].encode(f["W"].t()), ValueError)])
-def test_refused_calls_stay_refused(darb, fmt, bad):
+def test_refused_calls_stay_refused(darb, fmt, bad):  # noqa: F811
     call, err = bad
     with pytest.raises(darb.DarbError if err == "DarbError" else err):
         call(fmt)

@@ -1,35 +1,11 @@
 """GPU kernels at the edges of their tiles and dispatch rules, against the oracle."""
-import sys
-
 import numpy as np
 import pytest
 
 import oracle
-from tests._parity import compare
+from tests._gpu import darb, dev, host, say, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
-
-torch = pytest.importorskip("torch")
-
-
-def say(*a):
-    print(*a, flush=True, file=sys.stderr)
-
-
-@pytest.fixture(scope="module")
-def darb():
-    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
-    import paper_1911_08020_amd as d
-    return d
-
-
-def dev(a):
-    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
-
-
-def host(t):
-    torch.cuda.synchronize()
-    return t.cpu().numpy()
 
 
 # --------------------------------------------------------------------------------
@@ -40,7 +16,7 @@ def host(t):
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("N", [1, 5, 1023, 1024, 1025, 2047, 2049, 8193])
 @pytest.mark.parametrize("skip", [0, 1, 3])
-def test_encode_chunk_edges_any_alignment(darb, dtype, N, skip):
+def test_encode_chunk_edges_any_alignment(darb, dtype, N, skip):  # noqa: F811
     say(f"encode N={N} {np.dtype(dtype).name}, first element {skip} past an aligned one")
     rng = np.random.default_rng(N * 8 + skip)
     M, ldw = 7, N + skip
@@ -80,22 +56,29 @@ def _lstm_mats(darb, H, I, dtype, b_min, b_max, keep, seed):
 
 
 def _lstm_reference(wih, whh, x, h, c, T, B):
+    """Sequence, final states, and the largest sum of magnitudes that a gate adds up."""
     u = wih @ x.astype(np.float64)
+    ua = np.abs(wih) @ np.abs(x).astype(np.float64)
+    most = 0.0
     H = h.shape[0]
     seq = np.empty((H, T * B))
     sig = lambda z: 1.0 / (1.0 + np.exp(-z))  # noqa: E731
     for t in range(T):
         z = whh @ h + u[:, t * B:(t + 1) * B]
+        most = max(most, float((np.abs(whh) @ np.abs(h) + ua[:, t * B:(t + 1) * B]).max()))
         c = sig(z[H:2 * H]) * c + sig(z[:H]) * np.tanh(z[2 * H:3 * H])
         h = sig(z[3 * H:]) * np.tanh(c)
         seq[:, t * B:(t + 1) * B] = h
-    return seq, h, c
+    return seq, h, c, most
 
 
-# a gate sums at most 512 + 512 products of weights of about 0.1 and states below 1
-# (inputs of about 1): sum |w x| < 100, each rounding 2^-24, halved on average by the
-# cell: well below 1e-4 after the decay of earlier steps' errors
-LSTM_TOL = 1e-4
+# An fp32 sum whose magnitudes add up to S is off by a few S * 2^-24 (in a chain of a
+# thousand terms some 2^-24 S * sqrt(1000) / 4 at the very most, since partial sums grow as
+# they go), the activations and the cell by a few 2^-24 of values below 1 to T.  The gates'
+# slopes are at most 1, so a step adds its own error to what it inherits: T times the one of
+# a step bounds the last.
+def _lstm_tol(T, most):
+    return 4.0 * T * (most + 1.0) * 2.0 ** -24
 
 
 @pytest.mark.parametrize("case", [
@@ -106,7 +89,7 @@ LSTM_TOL = 1e-4
     (512, 64, 17, 20, "f32", 1, 4, 0.9), (512, 32, 16, 32, "f16", 1, 2, 0.9),
     (1024, 64, 16, 64, "f16", 4, 64, 0.05), (256, 64, 20, 40, "f32", 4, 64, 0.1),
     (1500, 64, 16, 20, "f16", 4, 64, 0.06), (64, 32, 15, 8, "f32", 4, 32, 0.1)])
-def test_lstm_sequence_launch(darb, case):
+def test_lstm_sequence_launch(darb, case):  # noqa: F811
     H, I, T, B, dt, b_min, b_max, keep = case
     say(f"lstm sequence {case}")
     dtype = np.float32 if dt == "f32" else np.float16
@@ -115,11 +98,11 @@ def test_lstm_sequence_launch(darb, case):
     h0 = (0.5 * rng.standard_normal((H, B))).astype(np.float32)
     c0 = rng.standard_normal((H, B)).astype(np.float32)
     seq, h, c = darb.lstm_layer(dih, dhh, dev(x), H, T, B, h=dev(h0), c=dev(c0))
-    rs, rh, rc = _lstm_reference(wih, whh, x, h0.astype(np.float64), c0.astype(np.float64), T, B)
+    rs, rh, rc, most = _lstm_reference(wih, whh, x, h0.astype(np.float64), c0.astype(np.float64), T, B)
     for got, want, name in ((seq, rs, "h_seq"), (h, rh, "h"), (c, rc, "c")):
         err = float(np.abs(host(got) - want).max())
-        say(f"  {name}: max abs err {err:.2e}")
-        assert err <= LSTM_TOL, name
+        say(f"  {name}: max abs err {err:.2e}, allowed {_lstm_tol(T, most):.2e}")
+        assert err <= _lstm_tol(T, most), name
     assert np.array_equal(host(h), host(seq)[:, (T - 1) * B:])
     # the same bits again, with the buffers as the first call left them
     again = darb.lstm_layer(dih, dhh, dev(x), H, T, B, h=dev(h0), c=dev(c0))
@@ -130,7 +113,7 @@ def test_lstm_sequence_launch(darb, case):
 @pytest.mark.parametrize("case", [(96, 16, 9, "f32", 4, 64, 0.1), (520, 17, 20, "f16", 4, 64, 0.1),
                                   (512, 18, 18, "f32", 2, 8, 0.3), (256, 40, 64, "f16", 4, 64, 0.1),
                                   (130, 50, 3, "f32", 4, 64, 0.1)])
-def test_lstm_sequence_forms(darb, case):
+def test_lstm_sequence_forms(darb, case):  # noqa: F811
     # the exchange of workgroups on one XCD and on different ones; and a workgroup allowed no
     # wait, which gives up at once, so that the last launch computes the sequence by itself:
     # the same bits
@@ -168,7 +151,7 @@ def _seq_flag(H, B):
     return 3 * H * (-(-B // cpg) * cpg)
 
 
-def test_lstm_sequences_on_several_streams(darb):
+def test_lstm_sequences_on_several_streams(darb):  # noqa: F811
     say("lstm sequences on three streams")
     H, T, B = 256, 40, 16
     _, (dih, dhh), rng = _lstm_mats(darb, H, 64, np.float16, 4, 64, 0.06, 3)
@@ -188,11 +171,15 @@ def test_lstm_sequences_on_several_streams(darb):
             assert torch.equal(a, b)
 
 
-def test_lstm_layer_under_capture(darb):
+def test_lstm_layer_under_capture(darb):  # noqa: F811
     say("lstm layer captured into a graph, replayed")
     H, T, B = 128, 16, 8
-    _, (dih, dhh), rng = _lstm_mats(darb, H, 64, np.float16, 4, 64, 0.06, 4)
-    x = dev(rng.standard_normal((64, T * B)).astype(np.float32))
+    # captured, each step is a launch, with sums of another order than the eager call's
+    (wih, whh), (dih, dhh), rng = _lstm_mats(darb, H, 64, np.float16, 4, 64, 0.06, 4)
+    xh = rng.standard_normal((64, T * B)).astype(np.float32)
+    x = dev(xh)
+    zero = np.zeros((H, B))
+    tol = _lstm_tol(T, _lstm_reference(wih, whh, xh, zero, zero, T, B)[3])
     want = [host(t) for t in darb.lstm_layer(dih, dhh, x, H, T, B)]
     h, c = torch.zeros(H, B, device="cuda"), torch.zeros(H, B, device="cuda")
     seq = torch.empty(H, T * B, device="cuda")
@@ -211,4 +198,4 @@ def test_lstm_layer_under_capture(darb):
         g.replay()
         torch.cuda.synchronize()
         for t, w in zip((seq, h, c), want):
-            assert np.abs(host(t) - w).max() <= LSTM_TOL
+            assert np.abs(host(t) - w).max() <= 2 * tol

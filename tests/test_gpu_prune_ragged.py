@@ -1,35 +1,12 @@
 """The pruning's sampled split at ragged sizes, against the oracle: rows of any length and
 alignment, rows of very different density."""
-import sys
-
 import numpy as np
 import pytest
 
 import oracle
+from tests._gpu import darb, dev, host, say, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
-
-torch = pytest.importorskip("torch")
-
-
-def say(*a):
-    print(*a, flush=True, file=sys.stderr)
-
-
-@pytest.fixture(scope="module")
-def darb():
-    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
-    import paper_1911_08020_amd as d
-    return d
-
-
-def dev(a):
-    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
-
-
-def host(t):
-    torch.cuda.synchronize()
-    return t.cpu().numpy()
 
 
 # 20 MiB is where the sampled split begins: just below, just above (fp32, fp16), rows shorter
@@ -38,7 +15,7 @@ def host(t):
 @pytest.mark.parametrize("M,N,skip", [(2621, 2000, 0), (2622, 2000, 0), (5242, 2000, 0),
                                       (5243, 2000, 0), (5243, 1001, 0),
                                       (1048600, 5, 0), (80000, 67, 1), (60000, 129, 0), (41, 131073, 3)])
-def test_prune_split_at_ragged_sizes(darb, dtype, M, N, skip):
+def test_prune_split_at_ragged_sizes(darb, dtype, M, N, skip):  # noqa: F811
     say(f"prune {M}x{N} {np.dtype(dtype).name} skip {skip}")
     rng = np.random.default_rng(M + N)
     W = rng.standard_normal((M, N), dtype=np.float32)
@@ -53,7 +30,7 @@ def test_prune_split_at_ragged_sizes(darb, dtype, M, N, skip):
         assert got.sum() == k
 
 
-def test_biased_pieces_fall_back_to_w(darb):
+def test_biased_pieces_fall_back_to_w(darb):  # noqa: F811
     # the sample's pieces are 16 vectors of 4 fp32 keys, 32 times that plus 37 vectors
     # apart: rows exactly one such stride long put every piece at the first 64 columns.
     # Values spread over 20 octaves only there propose a bracket near the top, while the

@@ -1,36 +1,13 @@
 """The SpMM at ragged sizes, against the oracle: batches that no vector divides, X from any
 element, rows that end inside a vector of weights, formats shorter than one."""
-import sys
-
 import numpy as np
 import pytest
 
 import oracle
+from tests._gpu import darb, dev, host, say, torch  # noqa: F401
 from tests._parity import compare
 
 pytestmark = pytest.mark.gpu
-
-torch = pytest.importorskip("torch")
-
-
-def say(*a):
-    print(*a, flush=True, file=sys.stderr)
-
-
-@pytest.fixture(scope="module")
-def darb():
-    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
-    import paper_1911_08020_amd as d
-    return d
-
-
-def dev(a):
-    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
-
-
-def host(t):
-    torch.cuda.synchronize()
-    return t.cpu().numpy()
 
 
 # lanes per row 1 .. 64, column remainders, rows of the last group that end inside a vector
@@ -40,7 +17,7 @@ def host(t):
     (1, 3, 2), (3, 5, 7), (5, 9, 1), (40, 301, 1), (40, 301, 2), (67, 1500, 3), (67, 301, 5),
     (33, 1027, 20), (2100, 130, 21), (2100, 130, 33), (50, 260, 34), (20, 333, 70),
     (2100, 96, 67), (9, 130, 257)])
-def test_spmm_ragged(darb, types, M, N, B):
+def test_spmm_ragged(darb, types, M, N, B):  # noqa: F811
     say(f"spmm {types} {M}x{N} B={B}")
     rng = np.random.default_rng(M * 7 + N + B)
     wdt = np.float16 if types.startswith("f16") else np.float32
