@@ -331,13 +331,14 @@ int darb_prune_counts_noalloc(int64_t M, int64_t N, int wdtype, const void *W, i
  * device, each once all that its own stream ordered before it has ended; a workgroup's
  * waits are bounded, and a sequence whose workgroups could not all run at once (another
  * process holding the device) is computed again without waiting, with the same result bit
- * for bit but some tens of milliseconds later.  Otherwise each time step is one launch: a workgroup per
- * hidden unit computes the unit's four gate rows of W_hh h_{t-1} and the cell
- * (batch <= 64 and a multiple of 4, or batch <= 16; W_hh rows of at most 512
- * retained weights); other shapes run
- * the recurrent product and the cell as two launches.  All give the same result
- * within the product tolerance; the call is deterministic.  The workspace also
- * holds the second buffer of h that the steps alternate with `h`, or the exchange's.
+ * for bit but some tens of milliseconds later.  Otherwise each time step is one launch: a
+ * workgroup per hidden unit computes the unit's four gate rows of W_hh h_{t-1} and the
+ * cell (batch <= 64 and a multiple of 4, or batch <= 16; W_hh rows of at most 512 retained
+ * weights); other shapes run the recurrent product and the cell as two launches.  The
+ * three add in different orders: they give the same result within the product tolerance,
+ * so a captured call, which takes no sequence launch, and an eager one may differ in the
+ * last bits.  For the same arguments the call is deterministic.  The workspace also holds
+ * the second buffer of h that the steps alternate with `h`, or the exchange's.
  *   x_seq      device fp32 [I x T*batch], column t*batch + n
  *   h_seq      device fp32 [H x T*batch], receives h_t in columns t*batch + n
  *   h, c       device fp32 [H x batch], initial state in, final state out

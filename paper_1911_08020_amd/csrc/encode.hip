@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "darb_internal.h"
+#include "row_vec.h"
 
 namespace darb {
 namespace {
@@ -188,17 +189,6 @@ __device__ __forceinline__ void small_blocks_all(const Vec<Bits, VEC> (&v)[UNROL
         small_blocks<Bits, VEC, LB>(v[u], cbase + int64_t(u) * (kWave * VEC) + int64_t(lane) * VEC,
                                     nblk, values, offsets);
 }
-
-// 16 bytes of a row at any element address: global loads need no alignment on gfx950,
-// so a row whose start is not a multiple of 16 bytes (N odd, an offset view) still takes
-// one load instruction per vector.
-template <typename Bits> struct RowVec;
-template <> struct RowVec<uint32_t> {
-    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <> struct RowVec<uint16_t> {
-    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(2)));
-};
 
 // Waves take (row, chunk) pairs one after the other, so a workgroup's four waves cover
 // several rows when a row is shorter than four chunks: a workgroup per row and four

@@ -622,8 +622,9 @@ struct SeqPlan {
 // leave at most 8 groups.
 bool seq_plan(const darb_plan &whh, int64_t H, int64_t T, int64_t batch, SeqPlan &p) {
     // setting up (the tables, the registers, two more launches) costs about as much as 8
-    // to 11 steps save: 56.8 against 50.1 us for T = 8 at H = 128, batch 32, but 105
-    // against 159 for T = 32; 91 / 90 and 217 / 324 at H = 1024
+    // to 11 steps save.  A layer of 16 steps, us, this way and with a launch per step, batch
+    // 1 / 8 / 16 / 64: H = 128 52 / 54 / 57 / 60 and 78 / 85 / 87 / 91, H = 1024 66 / 73 /
+    // 80 / 136 and 92 / 109 / 116 / 203
     if (T < 16 || batch > 64 || H < 16 || T > 0x7FFFFFFF) return false;
     // one workgroup per CU, an XCD's 32 for each group
     if (whh.cus < kSeqXcds * kSeqMembers) return false;

@@ -54,6 +54,7 @@
 #include <mutex>
 
 #include "darb_internal.h"
+#include "row_vec.h"
 
 namespace darb {
 namespace {
@@ -176,17 +177,6 @@ template <> struct PruneTraits<uint16_t> {
 constexpr int kFineBins = 1 << 14;
 
 template <typename Bits, int VEC> struct alignas(16) PVec { Bits e[VEC]; };
-
-// 16 bytes of a row at any element address: global loads need no alignment on gfx950, so
-// rows that do not start on 16 bytes (an odd N, an offset view) still take one load
-// instruction per vector.
-template <typename Bits> struct RowVec;
-template <> struct RowVec<uint32_t> {
-    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <> struct RowVec<uint16_t> {
-    typedef uint32_t T __attribute__((ext_vector_type(4), aligned(2)));
-};
 
 // Work is split evenly over the waves: W is taken as M rows padded to whole
 // VEC-element vectors, flattened, and wave w streams elements [w * per_wave,
