@@ -42,7 +42,7 @@
 // order, so the results are the same bits.
 //
 // H = 1024, T = 200, batch 32, fp16, 4.2 % kept: 2.9 us per step, against 7.3 us with a
-// launch per step; a layer with its input products 1660 -> 753 us.  A step spends 0.8 us
+// launch per step; a layer with its input products 1660 -> 741 us.  A step spends 0.8 us
 // until the last member's h arrives, 0.3 us to put it into LDS and meet, 1.1 us on the
 // gathers (LDS bank conflicts are about half of it), 0.4 us on the rows' sums and 0.3 us
 // on the cell and the stores.
