@@ -235,7 +235,7 @@ def recurrent_figures(args, with_cpu):
     """The recurrent workload: 2-layer LSTM, hidden 1024, T = 200, batch 32, fp16 DARB
     weights, fp32 state.  One sequence = both layers (darb_lstm_layer each).  The
     weights are encoded once before timing (model load) and stay cache-resident, as
-    in a serving loop.  Returns tokens/s, the per-step time of the fused step kernel
+    in a serving loop.  Returns tokens/s, the time of a step (its share of the sequence)
     and the two products' times."""
     import ctypes
 
@@ -298,7 +298,7 @@ def recurrent_figures(args, with_cpu):
         us = timer(lib.darb_spmm, a, reps)
         res[name] = {"avg_us": round(us, 3), "batch": B,
                      "gflops": round(2 * pl.nnz * B / (us * 1e-6) / 1e9, 1)}
-    # the fused time step: the layer's time minus its input product, over T steps
+    # a time step: the layer's time minus its input product, over T steps
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     wih, whh = layers[0]
     torch.cuda.synchronize()
